@@ -2,8 +2,9 @@
 
 Argument marshalling only: every function below forwards torch device
 tensors' pointers and sizes to the C entry point of the same name
-(include/dgq.h).  There is no CPU fallback: if the HIP library is missing or a
-call fails, an exception is raised.
+(include/dgq.h): the hot calls through native code (csrc/binding.cpp), the
+offline ones through ctypes.  There is no CPU fallback: if a library is missing
+or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
@@ -13,10 +14,12 @@ from dataclasses import dataclass
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libdgq.so")
+HOT_PATH = os.path.join(HERE, "_hot.so")
 
 DGQ_K_GRANULE = 64
 
 _lib = None
+_hot = None
 
 
 class DgqError(RuntimeError):
@@ -94,6 +97,26 @@ def lib():
         L.dgq_version.restype = C.c_int
         _lib = L
     return _lib
+
+
+def _load_hot():
+    """Load _hot.so (the hot calls' native side, linked against libdgq.so)."""
+    global _hot
+    import importlib.machinery
+    import importlib.util
+
+    import torch  # noqa: F401  its libraries first: _hot.so resolves against them
+    lib()
+    if not os.path.exists(HOT_PATH):
+        raise ImportError(
+            "_hot.so is not built: run `python -m paper_2501_04304_amd.build` "
+            "(or __graft_entry__.build()) first")
+    loader = importlib.machinery.ExtensionFileLoader("_hot", HOT_PATH)
+    m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_hot", loader))
+    loader.exec_module(m)
+    m.set_error_class(DgqError)
+    _hot = m
+    return m
 
 
 def _check(rc):
@@ -227,59 +250,20 @@ def dgq_groups_for_conv3x3(groups: Groups) -> Groups:
 def dgq_conv3x3_codes(groups9: Groups, codes, B: int, H: int, W: int, codes9=None, stream=None):
     """codes of the [B*H*W, C] map (dgq_quantize_act) -> the unfolded codes of its 3 x 3
     convolution, int8 in the layout of codes_shape(groups9, B*H*W)."""
-    import torch
-    _dev(codes, torch.int8, "codes")
-    rows = B * H * W
-    shape = codes_shape(groups9, rows)
-    if codes.numel() * 9 != shape[0] * shape[1] * shape[2]:
-        raise ValueError("codes do not belong to a [B*H*W, C] map of this layer")
-    if codes9 is None:
-        codes9 = torch.empty(shape, dtype=torch.int8, device=codes.device)
-    _dev(codes9, torch.int8, "codes9")
-    if tuple(codes9.shape) != shape:
-        raise ValueError("codes9 has the wrong shape")
-    _check(lib().dgq_conv3x3_codes(groups9.handle, _ptr(codes), B, H, W, _ptr(codes9), _stream(stream)))
-    return codes9
+    return (_hot or _load_hot()).conv3x3_codes(groups9, codes, B, H, W, codes9, stream)
 
 
 def dgq_quantize_act_conv3x3(groups: Groups, groups9: Groups, x, B: int, H: int, W: int, codes3=None,
                              row_class=None, stream=None):
     """x fp32 [B*H*W, C] -> (codes3, row_class): the three shifted copies of the map's codes that
     dgq_linear_conv3x3 gathers its nine taps from."""
-    import torch
-    _dev(x, torch.float32, "x")
-    rows = B * H * W
-    if tuple(x.shape) != (rows, groups.info.channels):
-        raise ValueError("x must be [B*H*W, C]")
-    nbytes = int(lib().dgq_conv3x3_codes3_bytes(groups9.handle, B, H, W))
-    if codes3 is None:
-        codes3 = torch.empty(nbytes, dtype=torch.int8, device=x.device)
-    if row_class is None:
-        row_class = torch.empty(rows, dtype=torch.uint8, device=x.device)
-    _dev(codes3, torch.int8, "codes3")
-    _dev(row_class, torch.uint8, "row_class")
-    if codes3.numel() != nbytes or row_class.numel() != rows:
-        raise ValueError("codes3 / row_class have the wrong size")
-    _check(lib().dgq_quantize_act_conv3x3(groups.handle, groups9.handle, _ptr(x), B, H, W, _ptr(codes3),
-                                          _ptr(row_class), _stream(stream)))
-    return codes3, row_class
+    return (_hot or _load_hot()).quantize_act_conv3x3(groups, groups9, x, B, H, W, codes3, row_class, stream)
 
 
 def dgq_linear_conv3x3(groups9: Groups, weight: "Weight", codes3, row_class, B: int, H: int, W: int, y=None,
                        stream=None):
     """The 3 x 3 convolution with its taps gathered by the contraction's loads: y fp32 [B*H*W, O]."""
-    import torch
-    _dev(codes3, torch.int8, "codes3")
-    _dev(row_class, torch.uint8, "row_class")
-    rows = B * H * W
-    if y is None:
-        y = torch.empty((rows, weight.out_channels), dtype=torch.float32, device=codes3.device)
-    _dev(y, torch.float32, "y")
-    if tuple(y.shape) != (rows, weight.out_channels):
-        raise ValueError("y has the wrong shape")
-    _check(lib().dgq_linear_conv3x3(groups9.handle, weight.handle, _ptr(codes3), _ptr(row_class), B, H, W,
-                                    _ptr(y), _stream(stream)))
-    return y
+    return (_hot or _load_hot()).linear_conv3x3(groups9, weight, codes3, row_class, B, H, W, y, stream)
 
 
 def dgq_pack_weight(groups: Groups, w, bias, w_bits: int, stream=None) -> Weight:
@@ -322,22 +306,7 @@ def codes_shape(groups: Groups, rows: int):
 
 def dgq_quantize_act(groups: Groups, x, codes=None, row_class=None, stream=None):
     """Returns (codes int8 [row blocks, chunks, 1024] block-tiled, row_class uint8 [rows])."""
-    import torch
-    _dev(x, torch.float32, "x")
-    rows, ch = x.shape
-    if ch != groups.info.channels:
-        raise ValueError("x has %d channels, the groups have %d" % (ch, groups.info.channels))
-    if codes is None:
-        codes = torch.empty(codes_shape(groups, rows), dtype=torch.int8, device=x.device)
-    if row_class is None:
-        row_class = torch.empty(rows, dtype=torch.uint8, device=x.device)
-    _dev(codes, torch.int8, "codes")
-    _dev(row_class, torch.uint8, "row_class")
-    if tuple(codes.shape) != codes_shape(groups, rows) or row_class.numel() != rows:
-        raise ValueError("codes / row_class have the wrong shape")
-    _check(lib().dgq_quantize_act(groups.handle, _ptr(x), rows, _ptr(codes), _ptr(row_class),
-                                  _stream(stream)))
-    return codes, row_class
+    return (_hot or _load_hot()).quantize_act(groups, x, codes, row_class, stream)
 
 
 def dgq_linear_workspace_bytes(groups: Groups, weight: Weight, rows: int) -> int:
@@ -348,73 +317,20 @@ def dgq_linear(groups: Groups, weight: Weight, codes, row_class, y=None, acc_dum
                stream=None, workspace=None):
     """Returns y fp32 [rows, O]; acc_dump (optional) int32 [rows, O, NG] is filled in place.
     workspace: uint8 device tensor of dgq_linear_workspace_bytes() bytes (nibble-packed weights)."""
-    import torch
-    _dev(codes, torch.int8, "codes")
-    _dev(row_class, torch.uint8, "row_class")
-    rows = row_class.numel()
-    if tuple(codes.shape) != codes_shape(groups, rows):
-        raise ValueError("codes / row_class have the wrong shape")
-    O = weight.out_channels
-    if y is None:
-        y = torch.empty((rows, O), dtype=torch.float32, device=codes.device)
-    _dev(y, torch.float32, "y")
-    if tuple(y.shape) != (rows, O):
-        raise ValueError("y has the wrong shape")
-    if acc_dump is not None:
-        _dev(acc_dump, torch.int32, "acc_dump")
-        if tuple(acc_dump.shape) != (rows, O, groups.info.n_groups):
-            raise ValueError("acc_dump has the wrong shape")
-    ws_ptr, ws_bytes = None, 0
-    if workspace is not None:
-        _dev(workspace, torch.uint8, "workspace")
-        ws_ptr, ws_bytes = _ptr(workspace), workspace.numel()
-    _check(lib().dgq_linear(groups.handle, weight.handle, _ptr(codes), _ptr(row_class), rows,
-                            _ptr(y), _ptr(acc_dump), ws_ptr, ws_bytes, _stream(stream)))
-    return y
+    return (_hot or _load_hot()).linear(groups, weight, codes, row_class, y, acc_dump, stream, workspace)
 
 
 def dgq_linear_geglu(groups: Groups, weight: Weight, codes, row_class, y=None, stream=None):
     """Returns fp32 [rows, O / 2]: first half of the layer's outputs times GELU(second half)."""
-    import torch
-    _dev(codes, torch.int8, "codes")
-    _dev(row_class, torch.uint8, "row_class")
-    rows = row_class.numel()
-    if tuple(codes.shape) != codes_shape(groups, rows):
-        raise ValueError("codes / row_class have the wrong shape")
-    oh = weight.out_channels // 2
-    if y is None:
-        y = torch.empty((rows, oh), dtype=torch.float32, device=codes.device)
-    _dev(y, torch.float32, "y")
-    if tuple(y.shape) != (rows, oh):
-        raise ValueError("y has the wrong shape")
-    _check(lib().dgq_linear_geglu(groups.handle, weight.handle, _ptr(codes), _ptr(row_class),
-                                  rows, _ptr(y), _stream(stream)))
-    return y
+    return (_hot or _load_hot()).linear_geglu(groups, weight, codes, row_class, y, stream)
 
 
 def dgq_linear_geglu_requant(groups: Groups, weight: Weight, codes, row_class, next_groups: Groups,
                              codes_next=None, row_class_next=None, stream=None):
     """Returns (codes_next, row_class_next): the following layer's codes of
     value * GELU(gate), in the layout of dgq_quantize_act(next_groups, .)."""
-    import torch
-    _dev(codes, torch.int8, "codes")
-    _dev(row_class, torch.uint8, "row_class")
-    rows = row_class.numel()
-    if tuple(codes.shape) != codes_shape(groups, rows):
-        raise ValueError("codes / row_class have the wrong shape")
-    shape = codes_shape(next_groups, rows)
-    if codes_next is None:
-        codes_next = torch.empty(shape, dtype=torch.int8, device=codes.device)
-    if row_class_next is None:
-        row_class_next = torch.empty(rows, dtype=torch.uint8, device=codes.device)
-    _dev(codes_next, torch.int8, "codes_next")
-    _dev(row_class_next, torch.uint8, "row_class_next")
-    if tuple(codes_next.shape) != shape or row_class_next.numel() != rows:
-        raise ValueError("codes_next / row_class_next have the wrong shape")
-    _check(lib().dgq_linear_geglu_requant(groups.handle, weight.handle, _ptr(codes), _ptr(row_class),
-                                          rows, _ptr(codes_next), _ptr(row_class_next),
-                                          _stream(stream)))
-    return codes_next, row_class_next
+    return (_hot or _load_hot()).linear_geglu_requant(groups, weight, codes, row_class, next_groups, codes_next,
+                                                      row_class_next, stream)
 
 
 def dgq_xattn_workspace_bytes(B, N, H, d, nk) -> int:
@@ -424,36 +340,8 @@ def dgq_xattn_workspace_bytes(B, N, H, d, nk) -> int:
 def dgq_xattn_logq(q, k, v, key_bias, attn_bits: int, out=None, scale_out=None, codes_dump=None,
                    workspace=None, stream=None):
     """q [B,N,H,d], k/v [B,nk,H,d] -> (out [B,N,H,d], scale [B])."""
-    import torch
-    _dev(q, torch.float32, "q")
-    _dev(k, torch.float32, "k")
-    _dev(v, torch.float32, "v")
-    if key_bias is not None:
-        _dev(key_bias, torch.float32, "key_bias")
-    B, N, H, d = q.shape
-    nk = k.shape[1]
-    if tuple(k.shape) != (B, nk, H, d) or tuple(v.shape) != (B, nk, H, d):
-        raise ValueError("k / v have the wrong shape")
-    if key_bias is not None and key_bias.numel() != nk:
-        raise ValueError("key_bias has the wrong shape")
-    if out is None:
-        out = torch.empty_like(q)
-    if scale_out is None:
-        scale_out = torch.empty(B, dtype=torch.float32, device=q.device)
-    _dev(out, torch.float32, "out")
-    _dev(scale_out, torch.float32, "scale_out")
-    if codes_dump is not None:
-        _dev(codes_dump, torch.uint8, "codes_dump")
-        if tuple(codes_dump.shape) != (B, H, N, nk - 1):
-            raise ValueError("codes_dump has the wrong shape")
-    need = dgq_xattn_workspace_bytes(B, N, H, d, nk)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    wbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(lib().dgq_xattn_logq(_ptr(q), _ptr(k), _ptr(v), _ptr(key_bias), B, N, H, d, nk,
-                                attn_bits, _ptr(out), _ptr(scale_out), _ptr(codes_dump),
-                                _ptr(workspace), wbytes, _stream(stream)))
-    return out, scale_out
+    return (_hot or _load_hot()).xattn_logq(q, k, v, key_bias, attn_bits, out, scale_out, codes_dump, workspace,
+                                            stream)
 
 
 def dgq_xattn_logq_intv(q, k, v_codes, v_params, key_bias, attn_bits: int = 4, out=None, scale_out=None,
@@ -526,28 +414,8 @@ def dgq_selfattn_logq(q, k, v, attn_bits: int, scale_in, out=None, scale_out=Non
                       workspace=None, stream=None):
     """q, k, v fp32 [B,N,H,d], scale_in fp32 [B] -> out fp32 [B,N,H,d].  scale_out [B] and
     codes_dump u8 [B,H,N,N] are filled if given."""
-    import torch
-    for t, name in ((q, "q"), (k, "k"), (v, "v"), (scale_in, "scale_in")):
-        _dev(t, torch.float32, name)
-    B, N, H, d = q.shape
-    if tuple(k.shape) != (B, N, H, d) or tuple(v.shape) != (B, N, H, d) or scale_in.numel() != B:
-        raise ValueError("q, k, v must share one shape [B,N,H,d] and scale_in have B entries")
-    if out is None:
-        out = torch.empty_like(q)
-    _dev(out, torch.float32, "out")
-    if scale_out is not None:
-        _dev(scale_out, torch.float32, "scale_out")
-    if codes_dump is not None:
-        _dev(codes_dump, torch.uint8, "codes_dump")
-        if tuple(codes_dump.shape) != (B, H, N, N):
-            raise ValueError("codes_dump must be [B,H,N,N]")
-    need = dgq_selfattn_workspace_bytes(B, N, H, d)
-    if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-    _check(lib().dgq_selfattn_logq(_ptr(q), _ptr(k), _ptr(v), B, N, H, d, attn_bits, _ptr(scale_in),
-                                   _ptr(out), _ptr(scale_out), _ptr(codes_dump), _ptr(workspace),
-                                   workspace.numel(), _stream(stream)))
-    return out
+    return (_hot or _load_hot()).selfattn_logq(q, k, v, attn_bits, scale_in, out, scale_out, codes_dump, workspace,
+                                               stream)
 
 
 def dgq_quantize_value(v, v_bits: int = 8, v_hat=None, want_codes: bool = False,
@@ -569,19 +437,5 @@ def dgq_quantize_value(v, v_bits: int = 8, v_hat=None, want_codes: bool = False,
 def dgq_xattn_logq_static(q, k, v, key_bias, attn_bits: int, scale_in, out=None, scale_out=None,
                           codes_dump=None, stream=None):
     """Attention with a given prompt scale (one pass).  Returns (out, scale_out or None)."""
-    import torch
-    _dev(q, torch.float32, "q")
-    _dev(k, torch.float32, "k")
-    _dev(v, torch.float32, "v")
-    _dev(scale_in, torch.float32, "scale_in")
-    B, N, H, d = q.shape
-    nk = k.shape[1]
-    if out is None:
-        out = torch.empty_like(q)
-    _check(lib().dgq_xattn_logq_static(_ptr(q), _ptr(k), _ptr(v),
-                                       _ptr(key_bias) if key_bias is not None else None, B, N, H, d,
-                                       nk, attn_bits, _ptr(scale_in), _ptr(out),
-                                       _ptr(scale_out) if scale_out is not None else None,
-                                       _ptr(codes_dump) if codes_dump is not None else None,
-                                       _stream(stream)))
-    return out, scale_out
+    return (_hot or _load_hot()).xattn_logq_static(q, k, v, key_bias, attn_bits, scale_in, out, scale_out,
+                                                   codes_dump, stream)
