@@ -212,7 +212,7 @@ int upload_tables(Groups *g) {
     const int32_t T = g->n_tab;
     g->n_chunks = (int32_t)g->perm.size() / kGranule;
     (void)hipGetDevice(&g->device);
-    std::vector<float> chunk_z((size_t)T * g->n_chunks), chunk_inv((size_t)T * g->n_chunks);
+    std::vector<float> chunk_z((size_t)T * g->n_chunks), chunk_inv((size_t)T * g->n_chunks), chunk_s((size_t)T * g->n_chunks);
     std::vector<float> zoff((size_t)T * NG);
     std::vector<int32_t> gchunk(NG + 1);
     for (int32_t k = 0; k <= NG; ++k) gchunk[k] = g->goff[k] / kGranule;
@@ -221,6 +221,7 @@ int upload_tables(Groups *g) {
             for (int32_t ch = gchunk[k]; ch < gchunk[k + 1]; ++ch) {
                 chunk_z[(size_t)p * g->n_chunks + ch] = g->z[p * NG + k];
                 chunk_inv[(size_t)p * g->n_chunks + ch] = g->inv_s[p * NG + k];
+                chunk_s[(size_t)p * g->n_chunks + ch] = g->s[p * NG + k];
             }
             zoff[(size_t)p * NG + k] =
                 (float)((double)g->z[p * NG + k] + (double)g->info.code_offset * (double)g->s[p * NG + k]);
@@ -228,6 +229,7 @@ int upload_tables(Groups *g) {
     int rc = upload(&g->d_perm, g->perm);
     if (rc == DGQ_OK) rc = upload(&g->d_chunk_z, chunk_z);
     if (rc == DGQ_OK) rc = upload(&g->d_chunk_inv, chunk_inv);
+    if (rc == DGQ_OK) rc = upload(&g->d_chunk_s, chunk_s);
     if (rc == DGQ_OK) rc = upload(&g->d_s, g->s);
     if (rc == DGQ_OK) rc = upload(&g->d_z, g->z);
     if (rc == DGQ_OK) rc = upload(&g->d_zoff, zoff);
@@ -242,6 +244,7 @@ void release(Groups *g) {
     (void)hipFree(g->d_perm);
     (void)hipFree(g->d_chunk_z);
     (void)hipFree(g->d_chunk_inv);
+    (void)hipFree(g->d_chunk_s);
     (void)hipFree(g->d_s);
     (void)hipFree(g->d_z);
     (void)hipFree(g->d_zoff);

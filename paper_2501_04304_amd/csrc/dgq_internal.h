@@ -54,6 +54,7 @@ struct Groups {
     int32_t *d_perm = nullptr;     // [K'] original channel or -1
     float *d_chunk_z = nullptr;    // [n_tab][n_chunks]  offset of the chunk's group
     float *d_chunk_inv = nullptr;  // [n_tab][n_chunks]  1/s of the chunk's group
+    float *d_chunk_s = nullptr;    // [n_tab][n_chunks]  s of the chunk's group
     float *d_s = nullptr;          // [n_tab][NG]
     float *d_z = nullptr;          // [n_tab][NG]
     float *d_zoff = nullptr;       // [n_tab][NG]  z + code_offset * s

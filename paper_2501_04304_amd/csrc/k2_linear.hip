@@ -42,6 +42,7 @@
 #include <type_traits>
 
 #include "dgq_internal.h"
+#include "epilogue.h"
 
 namespace dgq {
 
@@ -82,27 +83,6 @@ __device__ inline void wait_chunks_pending(int32_t later) {
     }
 }
 
-// GELU(t) = t * Phi(t).  Phi through the rational approximation 7.1.26 of Abramowitz and
-// Stegun for erfc: with z = |t| / sqrt 2 and u = 1 / (1 + p z),
-//     erfc(z) = (a1 u + a2 u^2 + a3 u^3 + a4 u^4 + a5 u^5) exp(-z^2),   |error| <= 1.5e-7,
-// so Phi(t) = erfc(z) / 2 for t < 0 (no cancellation in the lower tail) and 1 - erfc(z) / 2
-// otherwise: absolute error of Phi below 1e-7 plus fp32 rounding, at a third of the
-// instructions of the library erf (which made the fused epilogue slower than the plain one).
-__device__ inline float gelu(float t) {
-    const float z = fabsf(t) * 0.70710678118654752f;
-    const float u = __builtin_amdgcn_rcpf(fmaf(0.3275911f, z, 1.0f));
-    float pl = fmaf(1.061405429f, u, -1.453152027f);
-    pl = fmaf(pl, u, 1.421413741f);
-    pl = fmaf(pl, u, -0.284496736f);
-    pl = fmaf(pl, u, 0.254829592f);
-    pl = pl * u;
-    // exp(-z^2) = 2^(-t^2 / 2 * log2 e)
-    const float e = __builtin_amdgcn_exp2f(t * t * -0.72134752044448170f);
-    const float half_erfc = 0.5f * pl * e;
-    const float phi = t < 0.0f ? half_erfc : 1.0f - half_erfc;
-    return t * phi;
-}
-
 // Tile shape: WR x WO wavefronts, each BR x BO blocks of 32 x 32 outputs.
 template <int ABITS_, int WR_, int WO_, int BR_, int BO_, int STAGES_, int OCC_>
 struct Cfg {
@@ -140,23 +120,8 @@ struct Cfg {
 // small LDS table, and the zero-point term is zoff[class] * (sw[o] * wsum[o]) + bias[o],
 // whose two class-independent rows arrive in place of zb[0] and zb[1].
 //
-// CONV: the layer is a 3 x 3 convolution (stride 1, zero padding 1) and the nine taps are
-// GATHERED by the direct-to-LDS loads instead of being unfolded in memory.  `codes` holds
-// three copies of the map's code tensor, copy c at codes + c * cv.copy_bytes: copy 1 is the map
-// itself, copy 0 / copy 2 hold in row r the code row of the pixel to the left / right of r
-// (the code of the value 0 where the image ends).  Tap t = 3 (dy + 1) + (dx + 1) of a 16-row
-// (32-row) block of output pixels is then the block dy image rows further in copy dx + 1 --
-// one contiguous 1 KiB piece per chunk, as for a linear layer -- or, outside the image, a block
-// of the code of 0 (cv.fill: one 1 KiB block per chunk).  Needs the image width to be a
-// multiple of the rows of a block.  The K' order is tap-major, K' = 9 K'_map.
-struct ConvGather {
-    int32_t w_blocks = 0;    // image width / rows per code block
-    int32_t height = 0;      // image height
-    int32_t chunks = 0;      // chunks per tap (K'_map / 64)
-    int64_t copy_bytes = 0;  // bytes of one copy of the code tensor
-    const int8_t *fill = nullptr;
-};
-
+// CONV: the layer is a 3 x 3 convolution whose nine taps are GATHERED by the direct-to-LDS loads
+// instead of being unfolded in memory (ConvGather).
 template <class CF, bool DUMP, int GEGLU, bool MULTI, bool CONV = false>
 __global__ __launch_bounds__(CF::THREADS, CF::OCC) void k_linear(
     const int8_t *__restrict__ codes, const uint8_t *__restrict__ row_class,
@@ -841,6 +806,26 @@ hipError_t launch_cfg(const Groups &g, const Weight &w, const int8_t *codes,
 }  // namespace
 
 
+// Tile shape of the ring kernel by the number of tiles it gives.  Four waves per SIMD in every shape: a
+// wave's fold waits for its own MFMAs, so it is the other waves that keep the matrix pipe busy meanwhile.
+//   3  128 x 128, 8 waves of 32 x 64, two workgroups per CU: fewest operand bytes per output; where its
+//      last round of 512 workgroups leaves a fifth of all rounds idle, the 64-row tiles (6 x 22 x 64 x 928 ->
+//      960 convolution, 528 tiles: 180 us against 163)
+//   2  64 x 128, 4 waves of 32 x 64, three ring stages, four workgroups per CU
+//   1  the same behind four stages, three workgroups per CU: no more than that are resident anyway below
+//      768 tiles, and the loop is unrolled by four (2964 x 1280 -> 1280: 17.2 us with three stages, 15.0 with four)
+//   0  64 x 64, 4 waves of 32 x 32: less than 1.75 of the wider tiles per CU leave some CUs with twice the
+//      work of others (8192 x 320 -> 320: 8.0 -> 6.9 us, 8192 x 1280 -> 320: 14.3 -> 12.1, 4096 x 2560 -> 640:
+//      16.5 -> 14.6)
+static int ring_shape(int64_t rows, int32_t O) {
+#ifdef DGQ_TUNING  // tuning builds only: a forced tile shape
+    if (const int v = tuning_value(kTuneLinearCfg); v >= 10) return v - 10;
+#endif
+    const int64_t t128 = ((rows + 127) / 128) * ((O + 127) / 128), t64x128 = ((rows + 63) / 64) * ((O + 127) / 128);
+    const int64_t rounds = (t128 + 511) / 512;
+    return t128 >= 512 && 5 * t128 >= 4 * 512 * rounds ? 3 : (t64x128 > 768 ? 2 : (t64x128 >= 448 ? 1 : 0));
+}
+
 // The 3 x 3 convolution with its taps gathered by the loads (see ConvGather): `codes3` are the
 // three shifted copies of the map's codes, g9 / w the replicated tables and the packed
 // [O, 9 C] kernel.
@@ -857,17 +842,18 @@ hipError_t launch_linear_conv3x3(const Groups &g9, const Weight &w, const int8_t
     cv.chunks = g9.base_kp / kGranule;
     cv.copy_bytes = ((rows + rpb - 1) / rpb) * (int64_t)cv.chunks * 1024;
     cv.fill = reinterpret_cast<const int8_t *>(g9.d_fill_blocks);
-    const int64_t t128 = ((rows + 127) / 128) * ((w.O + 127) / 128);
-    const int64_t t64x128 = ((rows + 63) / 64) * ((w.O + 127) / 128);
-    const int cfg = t128 >= 512 ? 4 : (t64x128 >= 256 ? 2 : 6);
-    if (cfg == 4)
-        return a8 ? launch_cfg<Cfg<8, 4, 2, 1, 2, 4, 4>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv)
-                  : launch_cfg<Cfg<4, 4, 2, 1, 2, 4, 4>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv);
-    if (cfg == 2)
-        return a8 ? launch_cfg<Cfg<8, 2, 2, 1, 2, 3, 4>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv)
-                  : launch_cfg<Cfg<4, 2, 2, 1, 2, 3, 4>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv);
-    return a8 ? launch_cfg<Cfg<8, 2, 2, 1, 1, 8, 4>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv)
-              : launch_cfg<Cfg<4, 2, 2, 1, 1, 8, 4>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv);
+    if (linear_direct_pays(g9, rows, w.O))
+        return launch_linear_direct(g9, w, codes3, row_class, rows, y, 0, nullptr, &cv, nullptr, st);
+#define DGQ_CONV(...)                                                                                               \
+    return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv) \
+              : launch_cfg<Cfg<4, __VA_ARGS__>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv)
+    switch (ring_shape(rows, w.O)) {
+        case 0: DGQ_CONV(2, 2, 1, 1, 4, 4);
+        case 1: DGQ_CONV(2, 2, 1, 2, 4, 4);
+        case 2: DGQ_CONV(2, 2, 1, 2, 3, 4);
+        default: DGQ_CONV(4, 2, 1, 2, 4, 4);
+    }
+#undef DGQ_CONV
 }
 
 hipError_t launch_linear(const Groups &g, const Weight &w, const int8_t *codes,
@@ -877,62 +863,49 @@ hipError_t launch_linear(const Groups &g, const Weight &w, const int8_t *codes,
     const bool multi = g.n_tab > 2;  // more than two pixel classes (one channel group)
     if (multi && (geglu || acc_dump || g.info.n_groups != 1)) return hipErrorInvalidValue;
     if (geglu == 2 && (!w.d_rq_zi || !w.d_rq_keep || !rq_cls)) return hipErrorInvalidValue;
-    // Four waves per SIMD in every shape: a wave's fold waits for its own MFMAs, so it is
-    // the other waves that keep the matrix pipe busy meanwhile.  Large problems take
-    // 128 x 128 tiles (fewer operand bytes per output), medium ones 64 x 128 tiles so that every CU still gets work, and
-    // problems with fewer tiles than CUs (the projections of the 77-token prompt) 64 x 64
-    // tiles of four 32 x 32 waves behind an 8-deep ring: there a workgroup is alone on its CU and only the
-    // depth of the ring hides the latency of the chunks.
-    const int64_t t128 = ((rows + 127) / 128) * ((w.O + 127) / 128);
-    const int64_t t64x128 = ((rows + 63) / 64) * ((w.O + 127) / 128);
-    int cfg = t128 >= 512 ? 4 : (t64x128 >= 256 ? 2 : 6);
-    // Wide outputs (32 column tiles and more: the first feed-forward projections) run 2-4 % fewer
-    // clocks on 64 x 128 tiles, four workgroups per CU, than on 128 x 128 (measured with the
-    // launch's clock counter on 65536 x 640 -> 5120 and 16384 x 1280 -> 10240, both code widths);
-    // every other large shape is 3-9 % slower there.
-    if (cfg == 4 && !geglu && (w.O + 127) / 128 >= 32) cfg = 2;
-#ifdef DGQ_TUNING  // tuning builds only: a forced tile shape
-    if (const int v = tuning_value(kTuneLinearCfg); v > 0) cfg = v;
-#endif
-#define DGQ_CASE(ID, ...)                                                                          \
-    case ID:                                                                                       \
-        if (geglu == 2)                                                                            \
-            return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, 2>(g, w, codes, row_class, rows, y, nullptr, st, rq_cls) \
-                      : launch_cfg<Cfg<4, __VA_ARGS__>, false, 2>(g, w, codes, row_class, rows, y, nullptr, st, rq_cls); \
-        if (geglu)                                                                                 \
-            return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, 1>(g, w, codes, row_class, rows, y, nullptr, st) \
-                      : launch_cfg<Cfg<4, __VA_ARGS__>, false, 1>(g, w, codes, row_class, rows, y, nullptr, st); \
-        if (acc_dump) /* the same tile shape as the plain launch, every group accumulator stored */ \
-            return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, true>(g, w, codes, row_class, rows, y, acc_dump, st) \
-                      : launch_cfg<Cfg<4, __VA_ARGS__>, true>(g, w, codes, row_class, rows, y, acc_dump, st); \
-        if (multi)                                                                                 \
-            return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, false, true>(g, w, codes, row_class, rows, y, nullptr, st) \
-                      : launch_cfg<Cfg<4, __VA_ARGS__>, false, false, true>(g, w, codes, row_class, rows, y, nullptr, st); \
-        return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false>(g, w, codes, row_class, rows, y, nullptr, st) \
-                  : launch_cfg<Cfg<4, __VA_ARGS__>, false>(g, w, codes, row_class, rows, y, nullptr, st)
-    switch (cfg) {
-        DGQ_CASE(2, 2, 2, 1, 2, 3, 4);  // 64 x 128, 4 waves of 32 x 64, four workgroups per CU
-        case 6:  // 64 x 64 behind an 8-stage ring: 4 waves of 32 x 32 (13-15 % faster on the
-                 // 1232-row projections than 2 waves of 32 x 64); the gated epilogue needs
-                 // two column blocks per wave and keeps the 2-wave shape
-            if (geglu == 2)
-                return a8 ? launch_cfg<Cfg<8, 2, 1, 1, 2, 8, 4>, false, 2>(g, w, codes, row_class, rows, y, nullptr, st, rq_cls)
-                          : launch_cfg<Cfg<4, 2, 1, 1, 2, 8, 4>, false, 2>(g, w, codes, row_class, rows, y, nullptr, st, rq_cls);
-            if (geglu)
-                return a8 ? launch_cfg<Cfg<8, 2, 1, 1, 2, 8, 4>, false, 1>(g, w, codes, row_class, rows, y, nullptr, st)
-                          : launch_cfg<Cfg<4, 2, 1, 1, 2, 8, 4>, false, 1>(g, w, codes, row_class, rows, y, nullptr, st);
-            if (acc_dump)
-                return a8 ? launch_cfg<Cfg<8, 2, 2, 1, 1, 8, 4>, true>(g, w, codes, row_class, rows, y, acc_dump, st)
-                          : launch_cfg<Cfg<4, 2, 2, 1, 1, 8, 4>, true>(g, w, codes, row_class, rows, y, acc_dump, st);
-            if (multi)
-                return a8 ? launch_cfg<Cfg<8, 2, 2, 1, 1, 8, 4>, false, false, true>(g, w, codes, row_class, rows, y, nullptr, st)
-                          : launch_cfg<Cfg<4, 2, 2, 1, 1, 8, 4>, false, false, true>(g, w, codes, row_class, rows, y, nullptr, st);
-            return a8 ? launch_cfg<Cfg<8, 2, 2, 1, 1, 8, 4>, false>(g, w, codes, row_class, rows, y, nullptr, st)
-                      : launch_cfg<Cfg<4, 2, 2, 1, 1, 8, 4>, false>(g, w, codes, row_class, rows, y, nullptr, st);
-        default:
-            DGQ_CASE(4, 4, 2, 1, 2, 4, 4);  // 128 x 128, 8 waves of 32 x 64, two workgroups per CU
+    // the gated forms decide by the layer's own channel count (8 C wide), so that a gated layer and its
+    // requantizing form, whose rows are padded, take the same kernel and give the same bits
+    if (linear_direct_pays(g, rows, geglu ? 8 * (int64_t)g.info.channels : w.O))
+        return launch_linear_direct(g, w, codes, row_class, rows, y, geglu, rq_cls, nullptr, acc_dump, st);
+    int shape = ring_shape(rows, w.O);
+    if (geglu) {
+        // the gated epilogue needs two column blocks per wave
+        if (shape < 2) shape = 2;
+    } else if (shape == 3 && (w.O + 127) / 128 >= 32) {
+        // Wide outputs (32 column tiles and more: the first feed-forward projections) run 2-4 % fewer
+        // clocks on 64 x 128 tiles, four workgroups per CU, than on 128 x 128 (measured with the
+        // launch's clock counter on 65536 x 640 -> 5120 and 16384 x 1280 -> 10240, both code widths);
+        // every other large shape is 3-9 % slower there.
+        shape = 2;
     }
-#undef DGQ_CASE
+#define DGQ_GATED(MODE, ...)                                                                                        \
+    return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, MODE>(g, w, codes, row_class, rows, y, nullptr, st, rq_cls)    \
+              : launch_cfg<Cfg<4, __VA_ARGS__>, false, MODE>(g, w, codes, row_class, rows, y, nullptr, st, rq_cls)
+    if (geglu == 2) {
+        if (shape == 2) DGQ_GATED(2, 2, 2, 1, 2, 3, 4);
+        DGQ_GATED(2, 4, 2, 1, 2, 4, 4);
+    }
+    if (geglu) {
+        if (shape == 2) DGQ_GATED(1, 2, 2, 1, 2, 3, 4);
+        DGQ_GATED(1, 4, 2, 1, 2, 4, 4);
+    }
+#undef DGQ_GATED
+#define DGQ_PLAIN(...)                                                                                              \
+    if (acc_dump) /* the same tile shape as the plain launch, every group accumulator stored */                     \
+        return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, true>(g, w, codes, row_class, rows, y, acc_dump, st)             \
+                  : launch_cfg<Cfg<4, __VA_ARGS__>, true>(g, w, codes, row_class, rows, y, acc_dump, st);            \
+    if (multi)                                                                                                      \
+        return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, 0, true>(g, w, codes, row_class, rows, y, nullptr, st)    \
+                  : launch_cfg<Cfg<4, __VA_ARGS__>, false, 0, true>(g, w, codes, row_class, rows, y, nullptr, st);   \
+    return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false>(g, w, codes, row_class, rows, y, nullptr, st)                 \
+              : launch_cfg<Cfg<4, __VA_ARGS__>, false>(g, w, codes, row_class, rows, y, nullptr, st)
+    switch (shape) {
+        case 0: DGQ_PLAIN(2, 2, 1, 1, 4, 4);
+        case 1: DGQ_PLAIN(2, 2, 1, 2, 4, 4);
+        case 2: DGQ_PLAIN(2, 2, 1, 2, 3, 4);
+        default: DGQ_PLAIN(4, 2, 1, 2, 4, 4);
+    }
+#undef DGQ_PLAIN
 }
 
 }  // namespace dgq

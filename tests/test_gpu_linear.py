@@ -133,6 +133,24 @@ def test_ragged_medium_and_large_tiles(dgq, oracle, B, N, C, O, G, ab):
     _run_layer(dgq, oracle, run, cal, ab, 8, G, 2, bias=bias, sample_rows=rows)
 
 
+@pytest.mark.parametrize("ab", [8, 4])
+@pytest.mark.parametrize("B,N,C,O,G", [
+    (1, 31, 64, 31, 64),       # fewer chunks than wavefronts share them, one block short of full both ways
+    (1, 32, 200, 32, 64),      # exactly one block
+    (1, 33, 320, 36, 64),      # one row and one piece of channels into the next blocks
+    (2, 40, 3072, 68, 128),    # a long chain of chunks, groups cut between wavefronts
+    (2, 1500, 320, 840, 64),   # the ring kernel's 64 x 64 tiles, ragged
+    (2, 1500, 640, 1290, 128),  # its 64 x 128 tiles behind four stages, ragged
+])
+def test_block_edges_of_the_small_and_medium_kernels(dgq, oracle, B, N, C, O, G, ab):
+    seed = 500 + C + O
+    run = di.linear_case(seed, B, N, C, O)
+    cal = di.linear_case(seed, B, N, C, O, calib=True)
+    bias = np.random.default_rng(seed).standard_normal(O).astype(np.float32)
+    rows = None if B * N <= 128 else tile_rows(B * N, seed)
+    _run_layer(dgq, oracle, run, cal, ab, 8, G, 2, bias=bias, sample_rows=rows)
+
+
 def test_config1_full(dgq, oracle):
     """16x16 latent, 512 x 1280 -> 1280, G = 128, A8W8, seed 0; calibrated both
     on fresh data (clipping occurs) and on the tensor itself."""
