@@ -226,7 +226,30 @@ int upload_tables(Groups *g) {
             zoff[(size_t)p * NG + k] =
                 (float)((double)g->z[p * NG + k] + (double)g->info.code_offset * (double)g->s[p * NG + k]);
         }
+    const int per = g->info.act_bits == 8 ? 4 : 8;  // positions per output dword of the quantizer
+    const int32_t n_dw = (int32_t)g->perm.size() / per, dw_pad = (n_dw + 63) / 64 * 64;
+    std::vector<uint32_t> q_off, q_keep;
+    std::vector<float2> q_zi;
+    if (g->info.channels <= 16383) {
+        g->q_steps = dw_pad / 64;
+        q_off.assign((size_t)dw_pad * per / 2, 0);
+        q_keep.assign(dw_pad, 0);
+        q_zi.assign((size_t)T * g->n_chunks, make_float2(0.0f, 0.0f));
+        for (size_t j = 0; j < g->perm.size(); ++j) {
+            if (g->perm[j] < 0) continue;
+            const int k = (int)(j % per);
+            q_off[j / 2] |= (uint32_t)g->perm[j] * 4u << (16 * (j & 1));
+            // 8 bit: byte k of the word; 4 bit: byte k % 4, low nibble for k < 4, high otherwise
+            q_keep[j / per] |= per == 4 ? 0xffu << (8 * k) : 0xfu << (8 * (k & 3) + 4 * (k >> 2));
+        }
+        for (int p = 0; p < T; ++p)
+            for (int32_t ch = 0; ch < g->n_chunks; ++ch)
+                q_zi[(size_t)p * g->n_chunks + ch] = make_float2(chunk_z[(size_t)p * g->n_chunks + ch], chunk_inv[(size_t)p * g->n_chunks + ch]);
+    }
     int rc = upload(&g->d_perm, g->perm);
+    if (rc == DGQ_OK && g->q_steps) rc = upload(&g->d_q_off, q_off);
+    if (rc == DGQ_OK && g->q_steps) rc = upload(&g->d_q_keep, q_keep);
+    if (rc == DGQ_OK && g->q_steps) rc = upload(&g->d_q_zi, q_zi);
     if (rc == DGQ_OK) rc = upload(&g->d_chunk_z, chunk_z);
     if (rc == DGQ_OK) rc = upload(&g->d_chunk_inv, chunk_inv);
     if (rc == DGQ_OK) rc = upload(&g->d_chunk_s, chunk_s);
@@ -245,6 +268,9 @@ void release(Groups *g) {
     (void)hipFree(g->d_chunk_z);
     (void)hipFree(g->d_chunk_inv);
     (void)hipFree(g->d_chunk_s);
+    (void)hipFree(g->d_q_off);
+    (void)hipFree(g->d_q_keep);
+    (void)hipFree(g->d_q_zi);
     (void)hipFree(g->d_s);
     (void)hipFree(g->d_z);
     (void)hipFree(g->d_zoff);
@@ -690,7 +716,7 @@ int dgq_quantize_act_conv3x3(const dgq_groups_t *h, const dgq_groups_t *h9, cons
         return fail(DGQ_EALIGN, "dgq_quantize_act_conv3x3: tensor not 16-byte aligned");
     if ((int64_t)B * H * W > ((int64_t)1 << 31))
         return fail(DGQ_EUNSUPPORTED, "dgq_quantize_act_conv3x3: too many pixels");
-    if (quantize_act_lds_bytes(*g) > 160 * 1024)
+    if (!quantize_act_fits(*g))
         return fail(DGQ_EUNSUPPORTED, "dgq_quantize_act_conv3x3: too many channels for the LDS row buffers");
     const int64_t rows = (int64_t)B * H * W;
     const int64_t copy_bytes = (int64_t)(dgq_conv3x3_codes3_bytes(h9, B, H, W) / 3);
@@ -922,8 +948,8 @@ int dgq_quantize_act(const dgq_groups_t *h, const float *x, int64_t rows, int8_t
     if (!aligned16(x) || !aligned16(codes))
         return fail(DGQ_EALIGN, "dgq_quantize_act: tensor not 16-byte aligned");
     const Groups *g = reinterpret_cast<const Groups *>(h);
-    if (quantize_act_lds_bytes(*g) > 160 * 1024)
-        return fail(DGQ_EUNSUPPORTED, "dgq_quantize_act: too many channels for the LDS row buffers (about 7500)");
+    if (!quantize_act_fits(*g))
+        return fail(DGQ_EUNSUPPORTED, "dgq_quantize_act: too many channels for the row buffers (about 8000)");
     DGQ_HIP(launch_quantize_act(*g, x, rows, codes, row_class, static_cast<hipStream_t>(stream)));
     return DGQ_OK;
 }

@@ -55,6 +55,12 @@ struct Groups {
     float *d_chunk_z = nullptr;    // [n_tab][n_chunks]  offset of the chunk's group
     float *d_chunk_inv = nullptr;  // [n_tab][n_chunks]  1/s of the chunk's group
     float *d_chunk_s = nullptr;    // [n_tab][n_chunks]  s of the chunk's group
+    // The quantizer's tables per output dword (4 positions at 8 bit, 8 at 4 bit; 64 dwords a step, padded to
+    // whole steps): byte offsets into a row of activations, two to a word, and the mask of real positions; then
+    // (z, 1/s) of every chunk of those steps, class by class.  Null where offsets do not fit 16 bits.
+    uint32_t *d_q_off = nullptr, *d_q_keep = nullptr;
+    float2 *d_q_zi = nullptr;      // [n_tab][q_steps * chunks per step]
+    int32_t q_steps = 0;
     float *d_s = nullptr;          // [n_tab][NG]
     float *d_z = nullptr;          // [n_tab][NG]
     float *d_zoff = nullptr;       // [n_tab][NG]  z + code_offset * s
@@ -121,7 +127,7 @@ hipError_t raise_lds_limit(LdsLimit &state, const void *kernel, int bytes);
 #ifdef DGQ_TUNING
 // Builds with -DDGQ_TUNING (never the shipped library) export dgq_tuning_set(key, value): launch
 // parameters a sweep wants to force.  0 = the library's own choice.
-enum TuneKey { kTuneLinearCfg = 0, kTuneSuperRows, kTuneQuantWgPerCu, kTuneXattnWgs, kTuneKeys };
+enum TuneKey { kTuneLinearCfg = 0, kTuneSuperRows, kTuneQuantRows, kTuneXattnWgs, kTuneKeys };
 int tuning_value(int key);
 #endif
 
@@ -165,8 +171,8 @@ hipError_t launch_quantize_act(const Groups &g, const float *x, int64_t rows, in
 hipError_t launch_linear_conv3x3(const Groups &g9, const Weight &w, const int8_t *codes3,
                                  const uint8_t *row_class, int32_t B, int32_t H, int32_t W, float *y,
                                  hipStream_t st);
-// LDS bytes a workgroup of the quantizer needs for this layer (tables + one row per wave).
-size_t quantize_act_lds_bytes(const Groups &g);
+// whether the layer's rows fit the quantizer's registers and LDS (at least 7500 channels do)
+bool quantize_act_fits(const Groups &g);
 
 // geglu 1: y is [rows, O / 2] and receives value * GELU(gate) (first / second half of the
 // output channels); needs O % 128 == 0 and no accumulator dump.  geglu 2: the same value

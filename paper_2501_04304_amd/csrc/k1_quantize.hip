@@ -6,24 +6,28 @@
 // HBM-bound: every fp32 input is read once (4 B) and one code is written
 // (1 B at 8 bit, 0.5 B at 4 bit), plus one class byte per row.
 //
-// One wavefront owns a row.  The row arrives in registers with 16-byte loads
-// (issued one row ahead, so the next row is in flight while the current one is
-// processed), is reduced to max/min with wave shuffles, and is parked in the
-// wave's LDS slice.  After the class decision every lane takes 4 (8-bit) or 8
-// (4-bit) consecutive OUTPUT positions, gathers the inputs from LDS through the
-// channel permutation, and writes one dword into the block-tiled code layout the
-// GEMM loads (64 contiguous bytes per row and chunk; the four waves of a
-// workgroup own four consecutive rows each of a 16-row block, so a 1 KiB block
-// is completed by one workgroup).  Loaded once per workgroup into LDS: the
-// permutation as byte offsets into the row slice (padding positions point at
-// channel 0), one keep-mask per output dword that clears the padding positions
-// of the packed word (so padding costs nothing per position), and the per-chunk
-// (z, 1/s) pairs.  Per position that leaves: one address add, the gather, subtract,
-// multiply, round, clamp and the byte pack.
+// A row belongs to one wavefront (W = 1) or to the four of a workgroup (W = 4).  It arrives in
+// registers with 16-byte loads, issued one row ahead, is reduced to max / min with wave shuffles, and is
+// parked in LDS.  After the class decision every lane takes 4 (8-bit) or 8 (4-bit) consecutive OUTPUT
+// positions per step, gathers the inputs from LDS through the channel permutation, and writes one dword
+// into the block-tiled code layout the contraction loads (64 contiguous bytes per row and chunk).
+//
+// What a lane needs for its output dwords -- the gather offsets (two 16-bit byte offsets to a register), the
+// mask that clears padding positions of the packed word, (z, 1/s) for both classes, the place in the tiled
+// row -- stays in REGISTERS for all of the wavefront's rows, read once from tables prepared with the
+// handle: no table build and no barrier before the first row, a quarter less LDS traffic per position, and LDS holds
+// nothing but the rows.  A row of more than 1280 channels is shared by four wavefronts instead (two row
+// buffers and one barrier per row): the tables still fit, and a CU holds twelve wavefronts where one row
+// per wavefront left it four.  So are the rows of a launch with few of them.
+//
+// The loop over rows stores without conditions (a lane past the last output dword repeats that
+// dword): then the wait for the prefetched row is a wait for exactly that row, while with one conditional
+// store it becomes a wait for every store before it as well, a write round trip per row (the classes, too,
+// are kept and stored once per wavefront).  Measured against the kernel that built its tables in LDS and
+// stored conditionally, us: 154 x 768 4.1 -> 2.8, 512 x 1280 5.0 -> 3.2, 8192 x 320 7.5 -> 4.7, 2964 x 1280 7.0 -> 5.7,
+// 65536 x 640 41.5 -> 37.0 (5.8 TB/s), 16384 x 1280 24.1 -> 21.2, 16384 x 5120 8-bit 98.8 -> 75.3 (5.6 TB/s), 4-bit
+// 88.7 -> 72.3 (5.2 TB/s); a copy reaches 4.9 TB/s.
 #include "dgq_internal.h"
-
-#include <cstdlib>
-#include <type_traits>
 
 namespace dgq {
 
@@ -88,77 +92,41 @@ __device__ inline float quant_pre(float x, float z, float inv_s) {
     return BITS == 8 ? u : __builtin_amdgcn_fmed3f(u, 0.0f, 15.0f);
 }
 
-// LDS: [off32: kPer u32 per output dword][keep: one u32 per output dword]
-//      [cz: classes x chunks float2][rows: 4 * C floats].
-// The tables are padded to whole steps of 64 output dwords (a step is what the 64 lanes
-// do at once), so a lane of the last, partly filled step reads valid table entries
-// (offset 0, keep-mask 0) and only its store is predicated.
-struct QuantLds {
-    int32_t n_dw, n_steps, n_dw_pad, nch_pad;
-    size_t off_bytes, keep_bytes, cz_bytes;
-    __host__ __device__ QuantLds(int32_t Kp, int bits, int classes) {
-        const int per = bits == 8 ? 4 : 8;
-        n_dw = Kp / per;
-        n_steps = (n_dw + 63) >> 6;
-        n_dw_pad = n_steps * 64;
-        nch_pad = n_dw_pad / (64 / per);
-        off_bytes = (size_t)n_dw_pad * per * 4;
-        keep_bytes = (size_t)n_dw_pad * 4;
-        cz_bytes = (size_t)classes * nch_pad * 8;
-    }
-    __host__ __device__ size_t table_bytes() const { return off_bytes + keep_bytes + cz_bytes; }
-};
-
-// NV: float4 registers per lane that hold one row (C <= NV * 256).
-template <int BITS, int NV>
+// NV: float4 per lane that hold the wavefront's share of a row; NS: its output dwords per lane.
+// CONV: the rows are the pixels of images conv_w wide and the codes are written three times for the
+// tap-gathering 3 x 3 convolution: copy 1 (codes + copy_bytes) is the map itself, copy 0 holds in row r the
+// codes of the pixel left of r, copy 2 of the pixel right of r, and the code of the value 0 (fill32, one dword
+// per output dword) where the image ends.
+template <int BITS, int W, int NV, int NS, bool CONV>
 __global__ __launch_bounds__(256) void k_quantize_act(
-    const float *__restrict__ x, int64_t rows, int32_t C, int32_t Kp, int32_t n_chunks,
-    const int32_t *__restrict__ perm, const float *__restrict__ chunk_z,
-    const float *__restrict__ chunk_inv, const float *__restrict__ taus, int32_t n_tau,
-    int8_t *__restrict__ codes, uint8_t *__restrict__ row_class, int32_t rpw_log2,
-    int32_t conv_w, int64_t copy_bytes, const uint32_t *__restrict__ fill32) {
-    // conv_w > 0: the rows are the pixels of images conv_w wide and the codes are written three
-    // times for the tap-gathering 3 x 3 convolution: copy 1 (codes + copy_bytes) is the map
-    // itself, copy 0 holds in row r the codes of the pixel left of r, copy 2 of the pixel right
-    // of r, and the code of the value 0 (fill32, one dword per output dword) where the image ends.
+    const float *__restrict__ x, int64_t rows, int32_t C, int32_t n_dw, int32_t n_chunks,
+    const uint32_t *__restrict__ q_off, const uint32_t *__restrict__ q_keep, const float2 *__restrict__ q_zi,
+    const float *__restrict__ taus, int32_t n_tau, int8_t *__restrict__ codes,
+    uint8_t *__restrict__ row_class, int32_t rows_per, int32_t conv_w, int64_t copy_bytes,
+    const uint32_t *__restrict__ fill32) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
-    constexpr int kPer = BITS == 8 ? 4 : 8;          // positions per output dword
-    constexpr int kDwPerChunk = 64 / kPer;           // 16 or 8
-    constexpr int kChunkStep = kWave / kDwPerChunk;  // chunks per step: 4 or 8
-    const QuantLds L(Kp, BITS, n_tau + 1);
-    uint32_t *off32 = reinterpret_cast<uint32_t *>(lds_raw);
-    uint32_t *keep = reinterpret_cast<uint32_t *>(lds_raw + L.off_bytes);
-    float2 *cz = reinterpret_cast<float2 *>(lds_raw + L.off_bytes + L.keep_bytes);
-    float *rowbuf = reinterpret_cast<float *>(lds_raw + L.table_bytes());
+    constexpr int kPer = BITS == 8 ? 4 : 8;
+    constexpr int kDwPerChunk = 64 / kPer;
     const int tid = threadIdx.x;
-    // the wave index as a scalar: rows, row pointers and classes are then wave-uniform
-    // values in scalar registers and the loads and stores take scalar bases
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    float *xs = rowbuf + (size_t)wave * C;  // this wave's copy of the row
-    const uint32_t c4n = (uint32_t)C >> 2;  // float4 per row
-    const int32_t n_dw = L.n_dw;
+    const int part = W == 1 ? 0 : wave;  // this wave's share of a row
+    float *xs = reinterpret_cast<float *>(lds_raw) + (W == 1 ? (size_t)wave * C : 0);
+    float2 *zi_tab = reinterpret_cast<float2 *>(lds_raw + (size_t)C * (W == 1 ? 16 : 8));  // more than two classes
+    __shared__ float2 ext[2][W];  // the waves' extremes of a row
+    const uint32_t c4n = (uint32_t)C >> 2;
+    const int64_t first = (W == 1 ? (int64_t)blockIdx.x * kWavesPerBlock + wave : (int64_t)blockIdx.x) * rows_per;
+    const int32_t n = first >= rows ? 0 : (int32_t)(rows - first < rows_per ? rows - first : rows_per);
 
-    // rows: a workgroup takes units of 4 << rpw_log2 consecutive rows, wave w the rows
-    // (w << rpw_log2) .. of the unit, one after the other.  rpw_log2 = 2: a unit is one
-    // 16-row block of the tiled code layout; rpw_log2 = 0 (few rows): a quarter of one,
-    // so that four times as many workgroups share the work.
-    const int32_t us = 2 + rpw_log2;
-    const int64_t n_units = (rows + (1 << us) - 1) >> us;
-    auto row_of = [&](int64_t it) -> int64_t {  // it-th row of this wave's sequence
-        const int64_t u = (int64_t)blockIdx.x + (it >> rpw_log2) * gridDim.x;
-        return u < n_units ? (u << us) + (wave << rpw_log2) + (it & ((1 << rpw_log2) - 1)) : rows;
-    };
-    // A lane index past the end of the row is clamped to the last valid one, which
-    // re-reads a value that is already part of the row, so max/min and the LDS copy are
-    // unaffected.
+    // An index past the end of the row is clamped to the last valid one, which re-reads a value that is
+    // already part of the row, so max / min and the LDS copy are unaffected.
     float4 v[NV];
     uint32_t cidx[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-        const uint32_t c = lane + k * kWave;
+        const uint32_t c = lane + (k * W + part) * kWave;
         cidx[k] = c < c4n ? c : c4n - 1;
     }
-    auto fetch = [&](int64_t r) {  // r < rows, wave-uniform
+    auto fetch = [&](int64_t r) __attribute__((always_inline)) {
         const float4 *x4 = reinterpret_cast<const float4 *>(x + r * C);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
@@ -168,166 +136,148 @@ __global__ __launch_bounds__(256) void k_quantize_act(
             v[k] = make_float4(t.x, t.y, t.z, t.w);
         }
     };
+    if (n > 0) fetch(first);
 
-    // the first row travels while the tables are built
-    int64_t it = 0;
-    int64_t r = row_of(0);
-    if (r < rows) fetch(r);
-
-    for (int32_t d = tid; d < L.n_dw_pad; d += 256) {
-        uint32_t m = 0;
+    // the tables of this lane's output dwords travel with the first row
+    uint32_t off[NS][kPer / 2], keep[NS], pos[NS];  // pos: place in the tiled row, before the row's slot swizzle
+    float z0[NS], i0[NS], z1[NS], i1[NS];
+    int32_t chunk[NS];
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int32_t j = d * kPer + k;
-            const int32_t c = j < Kp ? perm[j] : -1;
-            off32[j] = c >= 0 ? (uint32_t)c * 4u : 0u;
-            // 8 bit: byte k of the word; 4 bit: byte k % 4, low nibble for k < 4, high otherwise
-            const uint32_t field = BITS == 8 ? 0xffu << (8 * k) : 0xfu << (8 * (k & 3) + 4 * (k >> 2));
-            if (c >= 0) m |= field;
+    for (int t = 0; t < NS; ++t) {
+        const uint32_t d0 = lane + 64u * (t * W + part), d = d0 < (uint32_t)n_dw ? d0 : (uint32_t)n_dw - 1;
+        if constexpr (BITS == 8) {
+            const uint2 o = reinterpret_cast<const uint2 *>(q_off)[d];
+            off[t][0] = o.x; off[t][1] = o.y;
+        } else {
+            const uint4 o = reinterpret_cast<const uint4 *>(q_off)[d];
+            off[t][0] = o.x; off[t][1] = o.y; off[t][kPer / 2 - 2] = o.z; off[t][kPer / 2 - 1] = o.w;
         }
-        keep[d] = m;
+        keep[t] = q_keep[d];
+        chunk[t] = (int32_t)(d / kDwPerChunk);
+        const float2 c0 = q_zi[chunk[t]], c1 = q_zi[n_chunks + chunk[t]];
+        z0[t] = c0.x; i0[t] = c0.y; z1[t] = c1.x; i1[t] = c1.y;
+        pos[t] = (d / kDwPerChunk) * 1024u + (d % kDwPerChunk) * 4u;
     }
-    for (int32_t i = tid; i < (n_tau + 1) * L.nch_pad; i += 256) {
-        const int32_t p = i / L.nch_pad, ch = i - p * L.nch_pad;
-        cz[i] = ch < n_chunks ? make_float2(chunk_z[p * n_chunks + ch], chunk_inv[p * n_chunks + ch])
-                              : make_float2(0.0f, 0.0f);
-    }
-    __syncthreads();
-
-    // Output dword d of the row covers positions 4d..4d+3 (8 bit) or 8d..8d+7 (4 bit).
-    // Lane l handles dwords l, l + 64, ... (one per step); in the tiled layout that is a
-    // fixed place inside a 64-byte (32-byte) row segment and a chunk index that advances
-    // by 4 (8 bit) or 8 (4 bit) per step, so every table and the output are read and
-    // written at a per-lane base plus a multiple of the step.
-    const char *off_lane = reinterpret_cast<const char *>(off32) + lane * (kPer * 4);
-    const char *keep_lane = reinterpret_cast<const char *>(keep) + lane * 4;
-    const uint32_t slot_lane = BITS == 8 ? (lane >> 2) & 3 : (lane >> 2) & 1;  // 16-byte slot
-    const uint32_t out_lane = (uint32_t)(lane / kDwPerChunk) * 1024u + (lane & 3) * 4u;
-    const char *xsb = reinterpret_cast<const char *>(xs);
     // lane k holds threshold k: the class of a row is the number of thresholds below its
     // range (the nearest cluster centre), counted with one compare and a mask population count
     const float tau_lane = lane < n_tau ? taus[lane] : INFINITY;
-
-    while (true) {
-        // the sequence ends at the first unit index past the end; rows inside the last
-        // unit but past `rows` are skipped
-        const int64_t u = (int64_t)blockIdx.x + (it >> rpw_log2) * gridDim.x;
-        if (u >= n_units) break;
-        const int64_t r_next = row_of(it + 1);
-        if (r < rows) {
-            float mx = -INFINITY, mn = INFINITY;
-            float4 *s4 = reinterpret_cast<float4 *>(xs);
-#pragma unroll
-            for (int k = 0; k < NV; ++k) {
-                s4[cidx[k]] = v[k];
-                mx = max3(max3(v[k].x, v[k].y, v[k].z), v[k].w, mx);
-                mn = min3(min3(v[k].x, v[k].y, v[k].z), v[k].w, mn);
-            }
-            if (r_next < rows) fetch(r_next);  // in flight while this row is quantized
-            wave_max_min(mx, mn);
-            const int p = __builtin_popcountll(__ballot(__fsub_rn(mx, mn) > tau_lane));
-            if (lane == 0) row_class[r] = (uint8_t)p;
-            const char *cz_lane = reinterpret_cast<const char *>(cz + p * L.nch_pad + lane / kDwPerChunk);
-            // The LDS slice is private to this wave and a wave's LDS operations complete
-            // in issue order, so a compiler-level fence is all that is needed.
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-
-            // a row's place in the tiled layout: scalar base, per-lane 32-bit offset
-            auto row_base = [&](int64_t rr) -> int8_t * {
-                const uint32_t t = (uint32_t)rr & (BITS == 8 ? 15u : 31u);
-                return codes + (((rr >> (BITS == 8 ? 4 : 5)) * n_chunks) << 10) + t * (BITS == 8 ? 64u : 32u);
-            };
-            auto row_off = [&](int64_t rr) -> uint32_t {
-                const uint32_t t = (uint32_t)rr & (BITS == 8 ? 15u : 31u);
-                return (out_lane + ((slot_lane ^ (uint32_t)(BITS == 8 ? swz64((int)t) : swz32((int)t))) << 4)) ^
-                       (BITS == 8 ? 0u : (uint32_t)half32((int)t) << 3);  // 4 bit: halves swapped in rows 16..31
-            };
-            int8_t *out_row = row_base(r) + (conv_w > 0 ? copy_bytes : 0);
-            const uint32_t out_off = row_off(r);
-            // the shifted copies (tap-gathering convolution): this row's codes are the left
-            // neighbour of row r + 1 and the right neighbour of row r - 1 of the same image row
-            const int32_t wcol = conv_w > 0 ? (int32_t)(r % conv_w) : 0;
-            const bool to_left = conv_w > 0 && wcol + 1 < conv_w, to_right = conv_w > 0 && wcol > 0;
-            const bool fill_left = conv_w > 0 && wcol == 0, fill_right = conv_w > 0 && wcol + 1 == conv_w;
-            int8_t *rowL = to_left ? row_base(r + 1) : out_row;                       // copy 0, row r + 1
-            int8_t *rowR = to_right ? row_base(r - 1) + 2 * copy_bytes : out_row;     // copy 2, row r - 1
-            const uint32_t offL = to_left ? row_off(r + 1) : 0u, offR = to_right ? row_off(r - 1) : 0u;
-            int8_t *rowF = fill_left ? row_base(r) : row_base(r) + 2 * copy_bytes;     // copy 0 or 2, row r
-
-            // NT steps together, so that their LDS round trips overlap
-            auto steps = [&](auto nt_tag, const int32_t j0) __attribute__((always_inline)) {
-                constexpr int NT = decltype(nt_tag)::value;
-                uint32_t off[NT][kPer];
-                float2 zi[NT];
-                uint32_t km[NT];
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const uint32_t j = (uint32_t)(j0 + t);
-                    zi[t] = *reinterpret_cast<const float2 *>(cz_lane + j * (kChunkStep * 8));
-                    km[t] = *reinterpret_cast<const uint32_t *>(keep_lane + j * 256u);
-                    const uint4 o0 = *reinterpret_cast<const uint4 *>(off_lane + j * (64u * kPer * 4));
-                    off[t][0] = o0.x; off[t][1] = o0.y; off[t][2] = o0.z; off[t][3] = o0.w;
-                    if constexpr (BITS == 4) {
-                        const uint4 o1 = *reinterpret_cast<const uint4 *>(off_lane + j * (64u * kPer * 4) + 16);
-                        off[t][4] = o1.x; off[t][5] = o1.y; off[t][6] = o1.z; off[t][7] = o1.w;
-                    }
-                }
-                float xv[NT][kPer];
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-#pragma unroll
-                    for (int k = 0; k < kPer; ++k)
-                        xv[t][k] = *reinterpret_cast<const float *>(xsb + off[t][k]);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    uint32_t lo = 0, hi = 0;
-#pragma unroll
-                    for (int k = 0; k < kPer; ++k) {
-                        const float qf = quant_pre<BITS>(xv[t][k], zi[t].x, zi[t].y);
-                        // rounds, saturates and places byte k of the word
-                        if (k < 4)
-                            lo = __builtin_amdgcn_cvt_pk_u8_f32(qf, k, lo);
-                        else
-                            hi = __builtin_amdgcn_cvt_pk_u8_f32(qf, k - 4, hi);
-                    }
-                    // 8 bit: stored code = q - 128 = q ^ 0x80 per byte.  4 bit: byte i holds
-                    // position i (low nibble) and position i + 4 (high nibble).  Padding
-                    // positions are cleared to the stored value 0.
-                    const uint32_t word = (BITS == 8 ? (lo ^ 0x80808080u) : (lo | (hi << 4))) & km[t];
-                    const uint32_t j = (uint32_t)(j0 + t);
-                    if ((int32_t)(lane + 64u * j) < n_dw) {
-                        *reinterpret_cast<uint32_t *>(out_row + (out_off + j * (kChunkStep * 1024u))) = word;
-                        if (to_left) *reinterpret_cast<uint32_t *>(rowL + (offL + j * (kChunkStep * 1024u))) = word;
-                        if (to_right) *reinterpret_cast<uint32_t *>(rowR + (offR + j * (kChunkStep * 1024u))) = word;
-                        if (fill_left || fill_right) {
-                            const uint32_t fw = fill32[lane + 64u * j];
-                            *reinterpret_cast<uint32_t *>(rowF + (out_off + j * (kChunkStep * 1024u))) = fw;
-                            // a one-pixel-wide image has both neighbours outside
-                            if (fill_left && fill_right)
-                                *reinterpret_cast<uint32_t *>(row_base(r) + 2 * copy_bytes +
-                                                              (out_off + j * (kChunkStep * 1024u))) = fw;
-                        }
-                    }
-                }
-            };
-            int32_t j0 = 0;
-            for (; j0 + 4 <= L.n_steps; j0 += 4) steps(std::integral_constant<int, 4>{}, j0);
-            switch (L.n_steps - j0) {
-                case 3: steps(std::integral_constant<int, 3>{}, j0); break;
-                case 2: steps(std::integral_constant<int, 2>{}, j0); break;
-                case 1: steps(std::integral_constant<int, 1>{}, j0); break;
-                default: break;
-            }
-            // the next row overwrites xs
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        } else if (r_next < rows) {
-            fetch(r_next);
-        }
-        r = r_next;
-        ++it;
+    if (n_tau > 1) {
+        for (int32_t i = tid; i < (n_tau + 1) * n_chunks; i += 256) zi_tab[i] = q_zi[i];
+        __syncthreads();
     }
+    uint32_t cls = 0;  // lane i: the class of this wavefront's i-th row
+
+    // a row's place in the tiled layout: scalar base, and what its slot swizzle flips in a lane's place
+    auto row_base = [&](int64_t rr) -> int8_t * {
+        const uint32_t t = (uint32_t)rr & (BITS == 8 ? 15u : 31u);
+        return codes + (((rr >> (BITS == 8 ? 4 : 5)) * n_chunks) << 10) + t * (BITS == 8 ? 64u : 32u);
+    };
+    auto row_xor = [&](int64_t rr) -> uint32_t {
+        const uint32_t t = (uint32_t)rr & (BITS == 8 ? 15u : 31u);
+        return BITS == 8 ? (uint32_t)swz64((int)t) << 4 : ((uint32_t)swz32((int)t) << 4) | ((uint32_t)half32((int)t) << 3);
+    };
+    auto one_row = [&](const int32_t i, const bool more) __attribute__((always_inline)) {
+        const int64_t r = first + i;
+        float mx = -INFINITY, mn = INFINITY;
+        float *xrow = W == 1 ? xs : xs + (i & 1) * C;
+        float4 *s4 = reinterpret_cast<float4 *>(xrow);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            s4[cidx[k]] = v[k];
+            mx = max3(max3(v[k].x, v[k].y, v[k].z), v[k].w, mx);
+            mn = min3(min3(v[k].x, v[k].y, v[k].z), v[k].w, mn);
+        }
+        if (more) fetch(r + 1);
+        wave_max_min(mx, mn);
+        if (W > 1) {
+            if (lane == 0) ext[i & 1][wave] = make_float2(mx, mn);
+            // LDS only: a full barrier would also wait for the row being fetched.  One per row is enough,
+            // since the next row goes to the other buffer.
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const float2 e = ext[i & 1][w];
+                mx = fmaxf(mx, e.x);
+                mn = fminf(mn, e.y);
+            }
+            mx = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, mx)));
+            mn = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, mn)));
+        }
+        const char *xsb = reinterpret_cast<const char *>(xrow);
+        const int p = __builtin_popcountll(__ballot(__fsub_rn(mx, mn) > tau_lane));
+        cls = lane == i ? (uint32_t)p : cls;
+        // (W = 1) the slice is private to this wave and a wave's LDS operations complete in issue order, so a
+        // compiler-level fence is all that is needed
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+
+        int8_t *out_row = row_base(r) + (CONV ? copy_bytes : 0);
+        const uint32_t out_xor = row_xor(r);
+        float xv[NS][kPer];
+#pragma unroll
+        for (int t = 0; t < NS; ++t)
+#pragma unroll
+            for (int k = 0; k < kPer; ++k)
+                xv[t][k] = *reinterpret_cast<const float *>(xsb + ((off[t][k / 2] >> (16 * (k & 1))) & 0xffffu));
+        uint32_t word[NS];
+        const uint32_t second = p == 0 ? 0u : ~0u;  // a mask: a select would put the arrays in memory
+        auto pick = [&](float a, float b) {
+            return __uint_as_float((__float_as_uint(a) & ~second) | (__float_as_uint(b) & second));
+        };
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+            float z = pick(z0[t], z1[t]), is = pick(i0[t], i1[t]);
+            if (p > 1) {
+                const float2 zi = zi_tab[p * n_chunks + chunk[t]];
+                z = zi.x;
+                is = zi.y;
+            }
+            uint32_t lo = 0, hi = 0;
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const float qf = quant_pre<BITS>(xv[t][k], z, is);
+                if (k < 4)
+                    lo = __builtin_amdgcn_cvt_pk_u8_f32(qf, k, lo);
+                else
+                    hi = __builtin_amdgcn_cvt_pk_u8_f32(qf, k - 4, hi);
+            }
+            // 8 bit: stored code = q - 128 = q ^ 0x80 per byte.  4 bit: byte i holds position i (low
+            // nibble) and position i + 4 (high nibble).  Padding positions are cleared to the stored value 0.
+            word[t] = (BITS == 8 ? (lo ^ 0x80808080u) : (lo | (hi << 4))) & keep[t];
+            *reinterpret_cast<uint32_t *>(out_row + (pos[t] ^ out_xor)) = word[t];
+        }
+        if (CONV) {
+            // the shifted copies: this row's codes are the left neighbour of row r + 1 and the right
+            // neighbour of row r - 1 of the same image row
+            auto fill = [&](int t) { return fill32[(pos[t] >> 10) * kDwPerChunk + ((pos[t] & 1023u) >> 2)]; };
+            const int32_t wcol = (int32_t)(r % conv_w);
+            if (wcol + 1 < conv_w) {
+                int8_t *rowL = row_base(r + 1);
+                const uint32_t x2 = row_xor(r + 1);
+#pragma unroll
+                for (int t = 0; t < NS; ++t) *reinterpret_cast<uint32_t *>(rowL + (pos[t] ^ x2)) = word[t];
+            } else {
+                int8_t *rowF = row_base(r) + 2 * copy_bytes;
+#pragma unroll
+                for (int t = 0; t < NS; ++t) *reinterpret_cast<uint32_t *>(rowF + (pos[t] ^ out_xor)) = fill(t);
+            }
+            if (wcol > 0) {
+                int8_t *rowR = row_base(r - 1) + 2 * copy_bytes;
+                const uint32_t x2 = row_xor(r - 1);
+#pragma unroll
+                for (int t = 0; t < NS; ++t) *reinterpret_cast<uint32_t *>(rowR + (pos[t] ^ x2)) = word[t];
+            } else {
+                int8_t *rowF = row_base(r);
+#pragma unroll
+                for (int t = 0; t < NS; ++t) *reinterpret_cast<uint32_t *>(rowF + (pos[t] ^ out_xor)) = fill(t);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    for (int32_t i = 0; i + 1 < n; ++i) one_row(i, true);
+    if (n > 0) one_row(n - 1, false);
+    if (lane < n && part == 0) row_class[first + lane] = (uint8_t)cls;
 }
 
 // Fallback for channel counts that are not a multiple of 4 (no 16-byte loads):
@@ -337,9 +287,7 @@ __global__ __launch_bounds__(256) void k_quantize_act_any(
     const float *__restrict__ x, int64_t rows, int32_t C, int32_t Kp, int32_t n_chunks,
     const int32_t *__restrict__ perm, const float *__restrict__ chunk_z,
     const float *__restrict__ chunk_inv, const float *__restrict__ taus, int32_t n_tau,
-    int8_t *__restrict__ codes, uint8_t *__restrict__ row_class,
-    int32_t /*rpw_log2: unused, one row per wave*/, int32_t /*conv_w: not built here*/,
-    int64_t /*copy_bytes*/, const uint32_t * /*fill32*/) {
+    int8_t *__restrict__ codes, uint8_t *__restrict__ row_class) {
     extern __shared__ float lds[];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     float *xs = lds + (size_t)wave * C;
@@ -387,125 +335,105 @@ __global__ __launch_bounds__(256) void k_quantize_act_any(
     }
 }
 
-using Kern = void (*)(const float *, int64_t, int32_t, int32_t, int32_t, const int32_t *,
-                      const float *, const float *, const float *, int32_t, int8_t *, uint8_t *,
-                      int32_t, int32_t, int64_t, const uint32_t *);
-
-// A kernel instantiation and the state of its dynamic-LDS limit.
-// Workgroups of a kernel that one CU holds at a given LDS size, as the runtime's occupancy
-// calculation gives it (registers count too: the 640-channel kernel needs 71, seven
-// workgroups per CU where LDS alone would admit eight).  Remembered per device together with
-// the LDS size it was asked for.
-struct Residency {
-    std::atomic<uint64_t> v[kMaxDevices];  // (LDS bytes + 1) << 8 | workgroups per CU; 0 = not asked yet
-};
+using Kern = void (*)(const float *, int64_t, int32_t, int32_t, int32_t, const uint32_t *, const uint32_t *,
+                      const float2 *, const float *, int32_t, int8_t *, uint8_t *, int32_t, int32_t, int64_t,
+                      const uint32_t *);
 struct Picked {
     Kern kern;
     LdsLimit *lim;
-    Residency *res;
 };
-template <int BITS, int NV>
-Picked vec_kernel() {
+template <int BITS, int W, int NV, int NS, bool CONV>
+Picked picked() {
     static LdsLimit lim;
-    static Residency res;
-    return {k_quantize_act<BITS, NV>, &lim, &res};
-}
-hipError_t resident_workgroups(const Picked &k, size_t lds, int *per_cu) {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    const uint64_t key = (uint64_t)lds + 1;
-    const uint64_t cur = k.res->v[dev].load(std::memory_order_acquire);
-    if ((cur >> 8) == key) {
-        *per_cu = (int)(cur & 0xff);
-        return hipSuccess;
-    }
-    int n = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(k.kern), 256, lds);
-    if (e != hipSuccess) return e;
-    n = n < 1 ? 1 : (n > 255 ? 255 : n);
-    k.res->v[dev].store(key << 8 | (uint64_t)n, std::memory_order_release);
-    *per_cu = n;
-    return hipSuccess;
-}
-template <int BITS>
-Picked any_kernel() {
-    static LdsLimit lim;
-    return {k_quantize_act_any<BITS>, &lim, nullptr};
+    return {k_quantize_act<BITS, W, NV, NS, CONV>, &lim};
 }
 
-// NV = float4 loads per lane per row; exact for the usual channel counts (320 .. 5120).
-template <int BITS>
-Picked pick_vec(int32_t C) {
-    const int nv = (C + 255) / 256;
-    if (nv <= 2) return vec_kernel<BITS, 2>();
-    if (nv <= 3) return vec_kernel<BITS, 3>();
-    if (nv <= 5) return vec_kernel<BITS, 5>();
-    if (nv <= 8) return vec_kernel<BITS, 8>();
-    if (nv <= 10) return vec_kernel<BITS, 10>();
-    if (nv <= 20) return vec_kernel<BITS, 20>();
-    return vec_kernel<BITS, 40>();
+constexpr int kMostFloat4 = 8, kMostSteps = 10;  // of the widest four-wavefront kernel: 8192 channels
+
+// The smallest kernel that holds nv float4 and ns output dwords per lane.
+template <int BITS, bool CONV>
+Picked pick(int W, int nv, int ns) {
+#define DGQ_PICK(W_, NV, NS) \
+    if (W == W_ && nv <= NV && ns <= NS) return picked<BITS, W_, NV, NS, CONV>()
+    DGQ_PICK(1, 2, 2);
+    DGQ_PICK(1, 3, 3);
+    DGQ_PICK(1, 3, 5);
+    DGQ_PICK(1, 5, 6);
+    DGQ_PICK(1, 5, 8);
+    if constexpr (BITS == 4) {
+        DGQ_PICK(1, 8, 4);
+        DGQ_PICK(1, 10, 6);
+    }
+    DGQ_PICK(4, 2, 2);
+    DGQ_PICK(4, 3, 3);
+    DGQ_PICK(4, 5, 3);
+    DGQ_PICK(4, 5, 6);
+    DGQ_PICK(4, 8, 5);
+    DGQ_PICK(4, kMostFloat4, kMostSteps);
+#undef DGQ_PICK
+    return {nullptr, nullptr};
 }
+
+bool vectorised(const Groups &g) { return g.info.channels % 4 == 0; }
 
 }  // namespace
 
-size_t quantize_act_lds_bytes(const Groups &g) {
-    const int32_t C = g.info.channels;
-    const bool vec4 = (C % 4) == 0 && C < 65535;
-    const size_t rows_bytes = sizeof(float) * (size_t)C * kWavesPerBlock;
-    return vec4 ? QuantLds(g.info.k_padded, g.info.act_bits, g.n_tab).table_bytes() + rows_bytes
-                : rows_bytes;
+bool quantize_act_fits(const Groups &g) {
+    if (!vectorised(g)) return sizeof(float) * (size_t)g.info.channels * kWavesPerBlock <= 160 * 1024;
+    return g.info.channels <= 4 * 256 * kMostFloat4 && g.q_steps <= 4 * kMostSteps;
 }
 
 hipError_t launch_quantize_act(const Groups &g, const float *x, int64_t rows, int8_t *codes,
                                uint8_t *row_class, hipStream_t st, int32_t conv_w, int64_t copy_bytes,
                                const uint32_t *fill32) {
     const int32_t C = g.info.channels, Kp = g.info.k_padded;
-    const bool vec4 = (C % 4) == 0 && C < 65535;
-    if (conv_w > 0 && !vec4) return hipErrorInvalidValue;
-    Picked kern;
-    size_t lds;
-    int64_t blocks;
-    int32_t rpw_log2 = 2;
-    if (vec4) {
-        kern = g.info.act_bits == 8 ? pick_vec<8>(C) : pick_vec<4>(C);
-        lds = QuantLds(Kp, g.info.act_bits, g.n_tab).table_bytes() +
-              sizeof(float) * (size_t)C * kWavesPerBlock;
-        blocks = (rows + 15) / 16;
-        if (blocks < 256) {  // fewer 16-row blocks than CUs: quarter blocks, one row per wave
-            rpw_log2 = 0;
-            blocks = (rows + 3) / 4;
-        }
-        // As many workgroups as the chip holds at once, every one walking several units: one
-        // more than that and the last ones start when the first are done, with their whole
-        // share of the rows still to do on a mostly idle chip.
+    const bool a8 = g.info.act_bits == 8;
+    if (!quantize_act_fits(g)) return hipErrorInvalidValue;
+    if (!vectorised(g)) {
+        if (conv_w > 0) return hipErrorInvalidValue;
+        const size_t lds = sizeof(float) * (size_t)C * kWavesPerBlock;
+        auto kern = a8 ? k_quantize_act_any<8> : k_quantize_act_any<4>;
         if (lds > 64 * 1024) {
-            hipError_t e = raise_lds_limit(*kern.lim, reinterpret_cast<const void *>(kern.kern), 160 * 1024);
+            const hipError_t e = a8 ? DGQ_ENSURE_LDS(k_quantize_act_any<8>, 160 * 1024) : DGQ_ENSURE_LDS(k_quantize_act_any<4>, 160 * 1024);
             if (e != hipSuccess) return e;
         }
-        int per_cu = 1;
-        if (hipError_t e = resident_workgroups(kern, lds, &per_cu); e != hipSuccess) return e;
-        per_cu = per_cu > 8 ? 8 : per_cu;
-#ifdef DGQ_TUNING  // tuning builds only: cap on resident workgroups per CU
-        if (const int cap_t = tuning_value(kTuneQuantWgPerCu); cap_t > 0 && per_cu > cap_t) per_cu = cap_t;
-#endif
-        const int64_t cap = 256 * (int64_t)per_cu;
-        if (blocks > cap) blocks = cap;
-    } else {
-        kern = g.info.act_bits == 8 ? any_kernel<8>() : any_kernel<4>();
-        lds = sizeof(float) * (size_t)C * kWavesPerBlock;
-        blocks = (rows + kWavesPerBlock - 1) / kWavesPerBlock;
-        if (blocks > 2048) blocks = 2048;
+        const int64_t blocks = (rows + kWavesPerBlock - 1) / kWavesPerBlock;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), lds, st, x, rows, C, Kp,
+                           g.n_chunks, g.d_perm, g.d_chunk_z, g.d_chunk_inv, g.d_taus, g.n_tab - 1, codes, row_class);
+        return hipGetLastError();
     }
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
-    if (lds > 64 * 1024) {
-        hipError_t e = raise_lds_limit(*kern.lim, reinterpret_cast<const void *>(kern.kern), 160 * 1024);
+    // One wavefront per row where its registers hold the tables (1280 channels at 8 bit, 2560 at 4 bit) and
+    // there are rows enough for the chip's wavefronts; otherwise four.  (us, one / four: 512 x 1280 3.6 / 3.2, 1024 x 640
+    // 3.0 / 3.7, 2964 x 1280 5.6 / 6.4, 16384 x 2560 8-bit not built / 39.8, 4-bit 35.6 / 39.9)
+    auto wave_holds = [&] {
+        const int nv = (C + 255) / 256, ns = g.q_steps;
+        return (nv <= 5 && ns <= 8) || (!a8 && nv <= 10 && ns <= 6);
+    };
+    const int W = wave_holds() && !(rows <= 1024 && C >= 768) ? 1 : 4;
+    const int nv = (C + 256 * W - 1) / (256 * W), ns = (g.q_steps + W - 1) / W;
+    // Rows per wavefront (or per workgroup of four sharing them): as many as the chip's resident wavefronts leave
+    // over, which spares table reads, but at most four (more leaves the last ones uneven).  A wavefront with
+    // more than three output dwords per lane holds half the registers of a SIMD's quarter again: fewer are
+    // resident (8148 x 896 with 1728 positions: 14.2 us with one row each, 10.6 with four).
+    const int64_t slots = W == 4 ? 512 : (ns <= 3 ? 4096 : 2048);
+    const int64_t want = (rows + slots / 2) / slots;
+    int32_t per = (int32_t)(want < 1 ? 1 : (want > 4 ? 4 : want));
+#ifdef DGQ_TUNING  // tuning builds only
+    if (const int v = tuning_value(kTuneQuantRows); v > 0) per = v;
+#endif
+    const Picked k = conv_w > 0 ? (a8 ? pick<8, true>(W, nv, ns) : pick<4, true>(W, nv, ns))
+                                : (a8 ? pick<8, false>(W, nv, ns) : pick<4, false>(W, nv, ns));
+    if (!k.kern) return hipErrorInvalidValue;
+    const size_t lds = sizeof(float) * (size_t)C * (W == 1 ? kWavesPerBlock : 2) +
+                       (g.n_tab > 2 ? sizeof(float2) * (size_t)g.n_tab * g.n_chunks : 0);
+    if (lds > 60 * 1024) {
+        const hipError_t e = raise_lds_limit(*k.lim, reinterpret_cast<const void *>(k.kern), 128 * 1024);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern.kern, dim3((unsigned)blocks), dim3(256), lds, st, x, rows, C, Kp,
-                       g.n_chunks, g.d_perm, g.d_chunk_z, g.d_chunk_inv, g.d_taus, g.n_tab - 1, codes,
-                       row_class, rpw_log2, conv_w, copy_bytes, fill32);
+    const int64_t per_wg = W == 1 ? (int64_t)kWavesPerBlock * per : per;
+    hipLaunchKernelGGL(k.kern, dim3((unsigned)((rows + per_wg - 1) / per_wg)), dim3(256), lds, st, x, rows, C,
+                       Kp / (a8 ? 4 : 8), g.n_chunks, g.d_q_off, g.d_q_keep, g.d_q_zi, g.d_taus, g.n_tab - 1, codes,
+                       row_class, per, conv_w, copy_bytes, fill32);
     return hipGetLastError();
 }
 

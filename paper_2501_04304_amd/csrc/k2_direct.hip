@@ -4,11 +4,12 @@
 // There a launch is a latency chain: one workgroup per CU walks its K chunks one after the other
 // through wait, barrier, LDS read, matrix instruction and fold, 0.27 us per chunk whatever the tile,
 // while most of the chip idles.  So the chain is cut: the four wavefronts of a workgroup take a
-// quarter of the chunks each of the SAME 32 x 32 output block (with the gated activation: eight
-// wavefronts, four quarters of the value block and of the gate block), read their operand fragments
-// straight from memory into registers (two chunks ahead, no LDS ring, no barrier), and add up
+// quarter of the chunks each of the SAME 32 x 32 output block, read their operand fragments straight from memory into registers (two chunks ahead, no LDS ring, no barrier), and add up
 // through LDS once, at the end.
-//   - Every chunk is folded by itself with the scale of its group (one value per lane, read with the
+//   - The gated forms keep one wavefront per block (their layers are wide: there are blocks enough) and fold
+//     whole groups in order, exactly as the ring kernel does: their results meet a quantizer next, and
+//     a last bit that depends on the kernel would now and then become a different code.
+//   - Otherwise every chunk is folded by itself with the scale of its group (one value per lane, read with the
 //     fragments): no group bookkeeping, and a group may be cut between two wavefronts.
 //   - Channels are the matrix instruction's M index (registers) and activation rows its N index
 //     (lanes): a row's class then selects a per-lane scale, for any number of classes, and after
@@ -30,7 +31,8 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kSlices = 4;  // wavefronts that share the K range of a block (2 and 8 measured up to 10 % slower)
+// wavefronts that share the K range of a block (2 and 8 measured up to 10 % slower)
+constexpr int slices(int geglu) { return geglu ? 1 : 4; }
 constexpr int kAhead = 2;   // chunks in flight per wavefront (3 and 4 need registers that cost occupancy: slower)
 
 __global__ __launch_bounds__(256) void k_clear(int32_t *__restrict__ p, int64_t n) {
@@ -41,7 +43,7 @@ __global__ __launch_bounds__(256) void k_clear(int32_t *__restrict__ p, int64_t 
 // DUMP: the int32 sums of every (row, channel, group), added up over the group's chunks in acc_dump
 // (which starts at zero); the results keep their bits.
 template <int ABITS, int GEGLU, bool MULTI, bool CONV, bool DUMP>
-__global__ __launch_bounds__(64 * kSlices * (GEGLU ? 2 : 1), 4) void k_linear_direct(
+__global__ __launch_bounds__(64 * slices(GEGLU) * (GEGLU ? 2 : 1), 4) void k_linear_direct(
     const int8_t *__restrict__ codes, const uint8_t *__restrict__ row_class,
     const int8_t *__restrict__ wq, const float *__restrict__ sw, const float *__restrict__ zb,
     const float *__restrict__ chunk_s, const float *__restrict__ zoff_tab, int64_t rows, int32_t O,
@@ -49,7 +51,9 @@ __global__ __launch_bounds__(64 * kSlices * (GEGLU ? 2 : 1), 4) void k_linear_di
     float *__restrict__ y, const float2 *__restrict__ rq_zi, const uint8_t *__restrict__ rq_keep,
     uint8_t *__restrict__ rq_cls, int32_t rq_bits, ConvGather cv, int32_t *__restrict__ acc_dump,
     const int32_t *__restrict__ gchunk, int32_t NG) {
+    constexpr int kSlices = slices(GEGLU);
     constexpr int WO = GEGLU ? 2 : 1;       // column blocks of a workgroup: the channels, or value and gate
+    constexpr int kThreads = 64 * kSlices * WO;
     constexpr int PITCH = 32 * WO + 4;      // floats per row of a slice's partial sums
     constexpr int NA = ABITS == 8 ? 2 : 1;  // 16-byte activation fragments per chunk
     __shared__ __attribute__((aligned(16))) float part[kSlices][32 * PITCH];
@@ -164,25 +168,33 @@ __global__ __launch_bounds__(64 * kSlices * (GEGLU ? 2 : 1), 4) void k_linear_di
         return v4i{(int)(p & 0x0f0f0f0fu), (int)((p >> 4) & 0x0f0f0f0fu), (int)(q & 0x0f0f0f0fu),
                    (int)((q >> 4) & 0x0f0f0f0fu)};
     };
+    const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    v16i acc = zero;
+    int32_t g = 0, g_end = GEGLU ? gchunk[1] : 0;  // whole groups: the running one and its end
     auto step = [&](const bool more, Frag &fr, int32_t c) __attribute__((always_inline)) {
-        const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         const float s = fr.s;
-        v16i acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr.b[0], a_operand(fr, 0), zero, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr.b[0], a_operand(fr, 0), GEGLU ? acc : zero, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr.b[1], a_operand(fr, 1), acc, 0, 0, 0);
         if (DUMP) {
-            int32_t g = 0;
-            while (g + 1 < NG && gchunk[g + 1] <= c) ++g;
+            int32_t gd = 0;
+            while (gd + 1 < NG && gchunk[gd + 1] <= c) ++gd;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int32_t o = ch0 + 8 * (i >> 2) + 4 * kh + (i & 3);
-                if (r0 + m32 < rows && o < O) atomicAdd(acc_dump + ((r0 + m32) * O + o) * NG + g, acc[i]);
+                if (r0 + m32 < rows && o < O) atomicAdd(acc_dump + ((r0 + m32) * O + o) * NG + gd, acc[i]);
             }
         }
         if (more) load(fr, c + kAhead);
         // left alone the compiler interleaves several steps and runs out of registers
         __builtin_amdgcn_sched_barrier(0);
+        if (!GEGLU || c + 1 == g_end) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sum[i] = fmaf((float)acc[i], s, sum[i]);
+            for (int i = 0; i < 16; ++i) sum[i] = fmaf((float)acc[i], s, sum[i]);
+            if (GEGLU) {
+                acc = zero;
+                g_end = ++g < NG ? gchunk[g + 1] : 0;
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     int32_t c = c_begin;
@@ -201,73 +213,75 @@ __global__ __launch_bounds__(64 * kSlices * (GEGLU ? 2 : 1), 4) void k_linear_di
             make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
     __syncthreads();
 
-    const int rl = tid >> 3;  // row of the block; the gated form needs half of its threads
-    const int64_t row = r0 + rl;
-    const bool live = rl < 32 && row < rows;
-    float h[WO][4];
-    if (live) {
-        const int32_t cl = row_class[row];
-        const float zo = MULTI ? zoff_tab[cl] : 0.0f;
 #pragma unroll
-        for (int w = 0; w < WO; ++w) {
-            const float *p = &part[0][rl * PITCH + 32 * w + 4 * piece];
-            float4 v = *reinterpret_cast<const float4 *>(p);
-#pragma unroll
-            for (int k = 1; k < kSlices; ++k) {
-                const float4 u = *reinterpret_cast<const float4 *>(p + k * 32 * PITCH);
-                v = make_float4(v.x + u.x, v.y + u.y, v.z + u.z, v.w + u.w);
-            }
-            const float4 z0 = c_z0[w], z1 = c_z1[w];
-            const float4 z = MULTI ? make_float4(fmaf(zo, z0.x, z1.x), fmaf(zo, z0.y, z1.y), fmaf(zo, z0.z, z1.z), fmaf(zo, z0.w, z1.w))
-                                   : (cl ? z1 : z0);
-            h[w][0] = fmaf(c_sw[w].x, v.x, z.x);
-            h[w][1] = fmaf(c_sw[w].y, v.y, z.y);
-            h[w][2] = fmaf(c_sw[w].z, v.z, z.z);
-            h[w][3] = fmaf(c_sw[w].w, v.w, z.w);
-        }
-        if (GEGLU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) h[0][e] *= gelu(h[WO - 1][e]);
-        }
-    }
-    if (GEGLU == 2) {
-        // the next layer's quantizer, as in k_linear: the channels are that layer's positions
-        const int32_t chunk = oc >> 6, nch2 = O >> 7;
-        const float2 zi = rq_zi[chunk];
-        uint32_t pk = 0;
+    for (int rl = tid >> 3; rl < 32; rl += kThreads / 8) {  // row of the block
+        const int64_t row = r0 + rl;
+        const bool live = row < rows;
+        float h[WO][4];
         if (live) {
+            const int32_t cl = row_class[row];
+            const float zo = MULTI ? zoff_tab[cl] : 0.0f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float u = __fmul_rn(__fsub_rn(h[0][e], zi.x), zi.y);
-                if (rq_bits == 4) u = __builtin_amdgcn_fmed3f(u, 0.0f, 15.0f);
-                pk = __builtin_amdgcn_cvt_pk_u8_f32(u, e, pk);
+            for (int w = 0; w < WO; ++w) {
+                const float *p = &part[0][rl * PITCH + 32 * w + 4 * piece];
+                float4 v = *reinterpret_cast<const float4 *>(p);
+#pragma unroll
+                for (int k = 1; k < kSlices; ++k) {
+                    const float4 u = *reinterpret_cast<const float4 *>(p + k * 32 * PITCH);
+                    v = make_float4(v.x + u.x, v.y + u.y, v.z + u.z, v.w + u.w);
+                }
+                const float4 z0 = c_z0[w], z1 = c_z1[w];
+                const float4 z = MULTI ? make_float4(fmaf(zo, z0.x, z1.x), fmaf(zo, z0.y, z1.y), fmaf(zo, z0.z, z1.z), fmaf(zo, z0.w, z1.w))
+                                       : (cl ? z1 : z0);
+                h[w][0] = fmaf(c_sw[w].x, v.x, z.x);
+                h[w][1] = fmaf(c_sw[w].y, v.y, z.y);
+                h[w][2] = fmaf(c_sw[w].z, v.z, z.z);
+                h[w][3] = fmaf(c_sw[w].w, v.w, z.w);
             }
-            if (rq_bits == 8) pk ^= 0x80808080u;
-            pk &= *reinterpret_cast<const uint32_t *>(rq_keep + oc);
-        }
-        int8_t *out = reinterpret_cast<int8_t *>(y);
-        if (rq_bits == 4) {  // a dword holds eight positions: byte i those of i (low nibble) and i + 4
-            const uint32_t high = (uint32_t)__shfl_down((int)pk, 1, 64);
-            const int e8 = (oc & 63) >> 3;
-            if (live && !(piece & 1))
-                *reinterpret_cast<uint32_t *>(out + tiled32_offset(row, chunk, nch2, e8 >> 2) +
-                                              (((e8 & 3) ^ (2 * half32((int)(row & 31)))) << 2)) = pk | (high << 4);
-        } else if (live) {
-            const int e4 = (oc & 63) >> 2;
-            *reinterpret_cast<uint32_t *>(out + tiled64_offset(row, chunk, nch2, e4 >> 2) + ((e4 & 3) << 2)) = pk;
-        }
-        if (tile_o == 0 && live && piece == 0) rq_cls[row] = 0;
-        return;
-    }
-    if (!live) return;
-    const int32_t width = GEGLU ? O / 2 : O;
-    float *dst = y + row * width + oc;
-    if ((width & 3) == 0) {
-        if (oc < width) *reinterpret_cast<float4 *>(dst) = make_float4(h[0][0], h[0][1], h[0][2], h[0][3]);
-    } else {
+            if (GEGLU) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (oc + e < width) dst[e] = h[0][e];
+                for (int e = 0; e < 4; ++e) h[0][e] *= gelu(h[WO - 1][e]);
+            }
+        }
+        if (GEGLU == 2) {
+            // the next layer's quantizer, as in k_linear: the channels are that layer's positions
+            const int32_t chunk = oc >> 6, nch2 = O >> 7;
+            const float2 zi = rq_zi[chunk];
+            uint32_t pk = 0;
+            if (live) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float u = __fmul_rn(__fsub_rn(h[0][e], zi.x), zi.y);
+                    if (rq_bits == 4) u = __builtin_amdgcn_fmed3f(u, 0.0f, 15.0f);
+                    pk = __builtin_amdgcn_cvt_pk_u8_f32(u, e, pk);
+                }
+                if (rq_bits == 8) pk ^= 0x80808080u;
+                pk &= *reinterpret_cast<const uint32_t *>(rq_keep + oc);
+            }
+            int8_t *out = reinterpret_cast<int8_t *>(y);
+            if (rq_bits == 4) {  // a dword holds eight positions: byte i those of i (low nibble) and i + 4
+                const uint32_t high = (uint32_t)__shfl_down((int)pk, 1, 64);
+                const int e8 = (oc & 63) >> 3;
+                if (live && !(piece & 1))
+                    *reinterpret_cast<uint32_t *>(out + tiled32_offset(row, chunk, nch2, e8 >> 2) +
+                                                  (((e8 & 3) ^ (2 * half32((int)(row & 31)))) << 2)) = pk | (high << 4);
+            } else if (live) {
+                const int e4 = (oc & 63) >> 2;
+                *reinterpret_cast<uint32_t *>(out + tiled64_offset(row, chunk, nch2, e4 >> 2) + ((e4 & 3) << 2)) = pk;
+            }
+            if (tile_o == 0 && live && piece == 0) rq_cls[row] = 0;
+            continue;
+        }
+        if (!live) continue;
+        const int32_t width = GEGLU ? O / 2 : O;
+        float *dst = y + row * width + oc;
+        if ((width & 3) == 0) {
+            if (oc < width) *reinterpret_cast<float4 *>(dst) = make_float4(h[0][0], h[0][1], h[0][2], h[0][3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (oc + e < width) dst[e] = h[0][e];
+        }
     }
 }
 
@@ -281,7 +295,7 @@ hipError_t launch(const Groups &g, const Weight &w, const int8_t *codes, const u
         hipLaunchKernelGGL(k_clear, dim3((unsigned)(n > 2048 * 256 ? 2048 : (n + 255) / 256)), dim3(256), 0, st, acc_dump, n);
     }
     hipLaunchKernelGGL((k_linear_direct<ABITS, GEGLU, MULTI, CONV, DUMP>), dim3((unsigned)(per_xcd * 8)),
-                       dim3(64 * kSlices * (GEGLU ? 2 : 1)), 0, st, codes, row_class, w.d_wq, w.d_sw, w.d_zb,
+                       dim3(64 * slices(GEGLU) * (GEGLU ? 2 : 1)), 0, st, codes, row_class, w.d_wq, w.d_sw, w.d_zb,
                        g.d_chunk_s, g.d_zoff, rows, w.O, w.O_pad, g.n_chunks, tiles_r, tiles_o, per_xcd, y,
                        w.d_rq_zi, w.d_rq_keep, rq_cls, w.next_bits, cv, acc_dump, g.d_gchunk, g.info.n_groups);
     return hipGetLastError();

@@ -863,14 +863,15 @@ hipError_t launch_linear(const Groups &g, const Weight &w, const int8_t *codes,
     const bool multi = g.n_tab > 2;  // more than two pixel classes (one channel group)
     if (multi && (geglu || acc_dump || g.info.n_groups != 1)) return hipErrorInvalidValue;
     if (geglu == 2 && (!w.d_rq_zi || !w.d_rq_keep || !rq_cls)) return hipErrorInvalidValue;
-    // the gated forms decide by the layer's own channel count (8 C wide), so that a gated layer and its
-    // requantizing form, whose rows are padded, take the same kernel and give the same bits
-    if (linear_direct_pays(g, rows, geglu ? 8 * (int64_t)g.info.channels : w.O))
+    if (linear_direct_pays(g, rows, w.O))
         return launch_linear_direct(g, w, codes, row_class, rows, y, geglu, rq_cls, nullptr, acc_dump, st);
     int shape = ring_shape(rows, w.O);
     if (geglu) {
-        // the gated epilogue needs two column blocks per wave
-        if (shape < 2) shape = 2;
+        // The gated epilogue needs two column blocks per wave.  With few chunks it is a third of a tile's life,
+        // which more and smaller workgroups hide better (us, 64 x 128 / 128 x 128 tiles, requantizing: 8192 x 320 -> 2560
+        // 26 / 29, 65536 x 640 -> 5120 423 / 438, 16384 x 960 -> 7680 212 / 205; not requantizing: 5794 x 256 -> 2048 14.6 / 15.0,
+        // 65536 x 640 -> 5120 433 / 423).
+        if (shape < 2 || g.n_chunks < (geglu == 2 ? 12 : 9)) shape = 2;
     } else if (shape == 3 && (w.O + 127) / 128 >= 32) {
         // Wide outputs (32 column tiles and more: the first feed-forward projections) run 2-4 % fewer
         // clocks on 64 x 128 tiles, four workgroups per CU, than on 128 x 128 (measured with the

@@ -134,6 +134,31 @@ def test_ragged_medium_and_large_tiles(dgq, oracle, B, N, C, O, G, ab):
 
 
 @pytest.mark.parametrize("ab", [8, 4])
+@pytest.mark.parametrize("rows,C", [
+    (5, 256), (4099, 260),    # one wavefront per row; one and two rows each, a whole and a barely begun register
+    (1025, 1280), (1024, 1280), (7, 764),  # either side of the row count that shares a row among four wavefronts
+    (1030, 1284), (1030, 2560), (1030, 2564),  # and of the widths that do (8-bit and 4-bit codes)
+    (3, 5120), (2051, 5120), (6, 7168),
+])
+def test_quantizer_shapes(dgq, oracle, rows, C, ab):
+    """Codes and row classes, bit for bit, at the edges of the quantizer's variants."""
+    import torch
+    run = di.linear_case(700 + C, 1, rows, C, 8)
+    cal = di.linear_case(700 + C, 1, 64, C, 8, calib=True)
+    og = oracle.calibrate(cal["X"], ab, 64, 2)
+    gg = dgq.dgq_calibrate_groups(_dev(cal["X"]), ab, 64, 2)
+    codes, cls = dgq.dgq_quantize_act(gg, _dev(run["X"]))
+    torch.cuda.synchronize()
+    oq = oracle.quantize_act(og, run["X"])
+    q = codes_to_q(codes.cpu().numpy(), ab, og.Kp, rows)
+    real = og.perm >= 0
+    assert np.array_equal(cls.cpu().numpy(), oq["cls"])
+    assert np.array_equal(q[:, real], oq["q"][:, real])
+    assert np.all(q[:, ~real] == (128 if ab == 8 else 0))
+    gg.free()
+
+
+@pytest.mark.parametrize("ab", [8, 4])
 @pytest.mark.parametrize("B,N,C,O,G", [
     (1, 31, 64, 31, 64),       # fewer chunks than wavefronts share them, one block short of full both ways
     (1, 32, 200, 32, 64),      # exactly one block
