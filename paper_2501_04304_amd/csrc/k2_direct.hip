@@ -4,8 +4,8 @@
 // There a launch is a latency chain: one workgroup per CU walks its K chunks one after the other
 // through wait, barrier, LDS read, matrix instruction and fold, 0.27 us per chunk whatever the tile,
 // while most of the chip idles.  So the chain is cut: the four wavefronts of a workgroup take a
-// quarter of the chunks each of the SAME 32 x 32 output block, read their operand fragments straight from memory into registers (two chunks ahead, no LDS ring, no barrier), and add up
-// through LDS once, at the end.
+// quarter of the chunks each of the SAME 32 x 32 output block, read their operand fragments straight from
+// memory into registers (two chunks ahead, no LDS ring, no barrier), and add up through LDS once, at the end.
 //   - The gated forms keep one wavefront per block (their layers are wide: there are blocks enough) and fold
 //     whole groups in order, exactly as the ring kernel does: their results meet a quantizer next, and
 //     a last bit that depends on the kernel would now and then become a different code.
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(64 * slices(GEGLU) * (GEGLU ? 2 : 1), 4) void k_lin
     int32_t O_pad, int32_t n_chunks, int32_t tiles_r, int32_t tiles_o, int32_t per_xcd,
     float *__restrict__ y, const float2 *__restrict__ rq_zi, const uint8_t *__restrict__ rq_keep,
     uint8_t *__restrict__ rq_cls, int32_t rq_bits, ConvGather cv, int32_t *__restrict__ acc_dump,
-    const int32_t *__restrict__ gchunk, int32_t NG) {
+    const int32_t *__restrict__ gchunk, int32_t NG, int32_t n_tab) {
     constexpr int kSlices = slices(GEGLU);
     constexpr int WO = GEGLU ? 2 : 1;       // column blocks of a workgroup: the channels, or value and gate
     constexpr int kThreads = 64 * kSlices * WO;
@@ -92,7 +92,9 @@ __global__ __launch_bounds__(64 * slices(GEGLU) * (GEGLU ? 2 : 1), 4) void k_lin
     constexpr uint32_t kBStep = ABITS == 8 ? 32 : 16;  // between the two k-steps' slots (XOR)
 
     int32_t cls = row_class[r0 + m32 < rows ? r0 + m32 : rows - 1];
-    if (!MULTI) cls = cls != 0;
+    // a class the layer does not have reads the last one's scale, never past the tables
+    if (MULTI) cls = cls < n_tab ? cls : n_tab - 1;
+    else cls = cls != 0;
     const float *s_row = chunk_s + (int64_t)cls * n_chunks;
 
     // CONV: the lane's row block in the centre tap of copy 0, and which of the image rows above, at
@@ -219,7 +221,8 @@ __global__ __launch_bounds__(64 * slices(GEGLU) * (GEGLU ? 2 : 1), 4) void k_lin
         const bool live = row < rows;
         float h[WO][4];
         if (live) {
-            const int32_t cl = row_class[row];
+            int32_t cl = row_class[row];
+            if (MULTI) cl = cl < n_tab ? cl : n_tab - 1;
             const float zo = MULTI ? zoff_tab[cl] : 0.0f;
 #pragma unroll
             for (int w = 0; w < WO; ++w) {
@@ -297,7 +300,7 @@ hipError_t launch(const Groups &g, const Weight &w, const int8_t *codes, const u
     hipLaunchKernelGGL((k_linear_direct<ABITS, GEGLU, MULTI, CONV, DUMP>), dim3((unsigned)(per_xcd * 8)),
                        dim3(64 * slices(GEGLU) * (GEGLU ? 2 : 1)), 0, st, codes, row_class, w.d_wq, w.d_sw, w.d_zb,
                        g.d_chunk_s, g.d_zoff, rows, w.O, w.O_pad, g.n_chunks, tiles_r, tiles_o, per_xcd, y,
-                       w.d_rq_zi, w.d_rq_keep, rq_cls, w.next_bits, cv, acc_dump, g.d_gchunk, g.info.n_groups);
+                       w.d_rq_zi, w.d_rq_keep, rq_cls, w.next_bits, cv, acc_dump, g.d_gchunk, g.info.n_groups, g.n_tab);
     return hipGetLastError();
 }
 

@@ -178,6 +178,22 @@ def test_sdxl_scale_sampled(dgq, oracle, dim):
     _free(res)
 
 
+@pytest.mark.parametrize("ab", [8, 4])
+def test_class_beyond_the_table_on_few_rows(dgq, oracle, ab):
+    """A row whose class the layer does not have is read as one of the last class: the per-lane scale of the kernel
+    for few rows never comes from behind the tables.  The other rows keep their bits."""
+    import torch
+    run = di.linear_case(1003, 1, 70, 200, 72)
+    res = _run(dgq, oracle, run["X"], run["X"], run["W"], ab, 8, 4, 1)
+    last, beyond = res["cls_dev"].clone(), res["cls_dev"].clone()
+    last[[0, 33, 69]] = 3
+    beyond[[0, 33, 69]] = torch.tensor([4, 16, 255], dtype=torch.uint8, device="cuda")
+    want = dgq.dgq_linear(res["gg"], res["wt"], res["codes"], last)
+    got = dgq.dgq_linear(res["gg"], res["wt"], res["codes"], beyond)
+    assert torch.equal(got, want)
+    _free(res)
+
+
 def test_timestep_tables(dgq, oracle):
     """Eq. 7: one (S, Z) entry per denoising step.  Three steps whose activations differ in
     scale get their own handles; each step's tensor is coded with its own entry."""
