@@ -205,6 +205,30 @@ int upload(T **dst, const std::vector<T> &src) {
     return DGQ_OK;
 }
 
+// Several tables in one device allocation with one copy: a call of each costs the calibration 40 us or so a
+// table.  Every table starts at a multiple of 256 bytes and has at least 16.
+struct TableBlock {
+    struct Entry {
+        void **dst;
+        size_t at;
+    };
+    std::vector<uint8_t> bytes;
+    std::vector<Entry> entries;
+    template <class T>
+    void add(T **dst, const std::vector<T> &src) {
+        const size_t at = (bytes.size() + 255) / 256 * 256, n = src.size() * sizeof(T);
+        bytes.resize(at + std::max<size_t>(n, 16), 0);
+        if (n) std::memcpy(bytes.data() + at, src.data(), n);
+        entries.push_back({reinterpret_cast<void **>(dst), at});
+    }
+    int upload(void **block) {
+        DGQ_HIP(hipMalloc(block, bytes.size()));
+        for (const Entry &e : entries) *e.dst = static_cast<uint8_t *>(*block) + e.at;
+        DGQ_HIP(hipMemcpy(*block, bytes.data(), bytes.size(), hipMemcpyHostToDevice));
+        return DGQ_OK;
+    }
+};
+
 // Device copies of a finished host description: per-chunk (z, 1/s) rows for the
 // quantizer, scale and offset rows and group boundaries for the contraction, thresholds.
 int upload_tables(Groups *g) {
@@ -246,36 +270,28 @@ int upload_tables(Groups *g) {
             for (int32_t ch = 0; ch < g->n_chunks; ++ch)
                 q_zi[(size_t)p * g->n_chunks + ch] = make_float2(chunk_z[(size_t)p * g->n_chunks + ch], chunk_inv[(size_t)p * g->n_chunks + ch]);
     }
-    int rc = upload(&g->d_perm, g->perm);
-    if (rc == DGQ_OK && g->q_steps) rc = upload(&g->d_q_off, q_off);
-    if (rc == DGQ_OK && g->q_steps) rc = upload(&g->d_q_keep, q_keep);
-    if (rc == DGQ_OK && g->q_steps) rc = upload(&g->d_q_zi, q_zi);
-    if (rc == DGQ_OK) rc = upload(&g->d_chunk_z, chunk_z);
-    if (rc == DGQ_OK) rc = upload(&g->d_chunk_inv, chunk_inv);
-    if (rc == DGQ_OK) rc = upload(&g->d_chunk_s, chunk_s);
-    if (rc == DGQ_OK) rc = upload(&g->d_s, g->s);
-    if (rc == DGQ_OK) rc = upload(&g->d_z, g->z);
-    if (rc == DGQ_OK) rc = upload(&g->d_zoff, zoff);
-    if (rc == DGQ_OK) rc = upload(&g->d_taus, g->taus);
-    if (rc == DGQ_OK) rc = upload(&g->d_gchunk, gchunk);
-    return rc;
+    TableBlock t;
+    t.add(&g->d_perm, g->perm);
+    if (g->q_steps) {
+        t.add(&g->d_q_off, q_off);
+        t.add(&g->d_q_keep, q_keep);
+        t.add(&g->d_q_zi, q_zi);
+    }
+    t.add(&g->d_chunk_z, chunk_z);
+    t.add(&g->d_chunk_inv, chunk_inv);
+    t.add(&g->d_chunk_s, chunk_s);
+    t.add(&g->d_s, g->s);
+    t.add(&g->d_z, g->z);
+    t.add(&g->d_zoff, zoff);
+    t.add(&g->d_taus, g->taus);
+    t.add(&g->d_gchunk, gchunk);
+    return t.upload(&g->d_tables);
 }
 
 void release(Groups *g) {
     if (!g) return;
     if (g->refs.fetch_sub(1, std::memory_order_acq_rel) != 1) return;  // a weight handle still uses it
-    (void)hipFree(g->d_perm);
-    (void)hipFree(g->d_chunk_z);
-    (void)hipFree(g->d_chunk_inv);
-    (void)hipFree(g->d_chunk_s);
-    (void)hipFree(g->d_q_off);
-    (void)hipFree(g->d_q_keep);
-    (void)hipFree(g->d_q_zi);
-    (void)hipFree(g->d_s);
-    (void)hipFree(g->d_z);
-    (void)hipFree(g->d_zoff);
-    (void)hipFree(g->d_taus);
-    (void)hipFree(g->d_gchunk);
+    (void)hipFree(g->d_tables);
     (void)hipFree(g->d_fill);
     (void)hipFree(g->d_fill_blocks);
     delete g;

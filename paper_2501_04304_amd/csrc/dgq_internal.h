@@ -51,15 +51,16 @@ struct Groups {
     std::vector<float> s, z, inv_s;  // [n_tab][NG]
     std::vector<float> taus;         // [n_tab - 1] ascending row-range thresholds; +inf = unused
     // device tables
+    void *d_tables = nullptr;      // the allocation the tables below lie in (all but the fill rows)
     int32_t *d_perm = nullptr;     // [K'] original channel or -1
     float *d_chunk_z = nullptr;    // [n_tab][n_chunks]  offset of the chunk's group
     float *d_chunk_inv = nullptr;  // [n_tab][n_chunks]  1/s of the chunk's group
     float *d_chunk_s = nullptr;    // [n_tab][n_chunks]  s of the chunk's group
     // The quantizer's tables per output dword (4 positions at 8 bit, 8 at 4 bit; 64 dwords a step, padded to
     // whole steps): byte offsets into a row of activations, two to a word, and the mask of real positions; then
-    // (z, 1/s) of every chunk of those steps, class by class.  Null where offsets do not fit 16 bits.
+    // (z, 1/s) of every chunk, class by class.  Null where offsets do not fit 16 bits.
     uint32_t *d_q_off = nullptr, *d_q_keep = nullptr;
-    float2 *d_q_zi = nullptr;      // [n_tab][q_steps * chunks per step]
+    float2 *d_q_zi = nullptr;      // [n_tab][n_chunks]
     int32_t q_steps = 0;
     float *d_s = nullptr;          // [n_tab][NG]
     float *d_z = nullptr;          // [n_tab][NG]
