@@ -714,6 +714,11 @@ __device__ __host__ inline int v_row_slot(int t, int c) { return t * 64 + ((c ^ 
 #define DGQ_X_WAIT_VMCNT(N) \
     __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
+// Write-bound: a tile image is one 16-byte slot of K (eight dims of a key) and one of V^T (eight keys of a
+// dim) per thread and piece, each put together in registers and stored whole, four neighbouring lanes to a
+// 64-byte row of V^T, a row of K to eight.  (With one 8-byte piece of K and single bf16 elements of V^T per
+// store the launch took 24 us on 2 x 8 x 4096 x 40, 54 MB moved; now 12, and 54 us on 16 x 20 x 1024 x 64,
+// 335 MB at 6.2 TB/s.)
 template <class CF>
 __global__ __launch_bounds__(256) void k_selfattn_prep(
     const float *__restrict__ k, const float *__restrict__ v, int32_t nk, int32_t H, int32_t d,
@@ -731,33 +736,42 @@ __global__ __launch_bounds__(256) void k_selfattn_prep(
     uint8_t *img = ws + (bh * n_tiles + tile) * CF::TILE_BYTES;
     uint8_t *khp = img, *klp = img + 32 * CF::PITCH;
     uint8_t *vhp = img + CF::K_BYTES, *vlp = vhp + DV * 64;
-    constexpr int QUADS = CF::PITCH / 8;  // fours of dims per K row
-    for (int idx = tid; idx < 32 * QUADS; idx += 256) {
-        const int j = idx / QUADS, t4 = (idx - j * QUADS) * 4;
+    constexpr int SLOTS = CF::PITCH / 16;  // eights of dims per K row
+    for (int idx = tid; idx < 32 * SLOTS; idx += 256) {
+        const int j = idx / SLOTS, c = idx - j * SLOTS, t8 = 8 * c;
         const int32_t key = 32 * tile + j;
-        float4 x = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (key < nk && t4 < d) x = *reinterpret_cast<const float4 *>(kb + (int64_t)key * hs + t4);
+        const float *p = kb + (int64_t)key * hs + t8;
+        float4 x = {0.0f, 0.0f, 0.0f, 0.0f}, y = x;
+        if (key < nk && t8 < d) x = *reinterpret_cast<const float4 *>(p);
+        if (key < nk && t8 + 4 < d) y = *reinterpret_cast<const float4 *>(p + 4);
         const HiLo p0 = split_h2(x.x * qk_scale, x.y * qk_scale);
         const HiLo p1 = split_h2(x.z * qk_scale, x.w * qk_scale);
-        const int off = k_row_slot(CF::PITCH, j, t4 >> 3) + (t4 & 7) * 2;
-        *reinterpret_cast<u32x2 *>(khp + off) = u32x2{p0.hi, p1.hi};
-        *reinterpret_cast<u32x2 *>(klp + off) = u32x2{p0.lo, p1.lo};
+        const HiLo p2 = split_h2(y.x * qk_scale, y.y * qk_scale);
+        const HiLo p3 = split_h2(y.z * qk_scale, y.w * qk_scale);
+        const int off = k_row_slot(CF::PITCH, j, c);
+        *reinterpret_cast<u32x4 *>(khp + off) = u32x4{p0.hi, p1.hi, p2.hi, p3.hi};
+        *reinterpret_cast<u32x4 *>(klp + off) = u32x4{p0.lo, p1.lo, p2.lo, p3.lo};
     }
-    for (int idx = tid; idx < 32 * (DV / 4); idx += 256) {
-        const int j = idx / (DV / 4), t4 = (idx - j * (DV / 4)) * 4;
-        const int32_t key = 32 * tile + j;
-        float4 x = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (key < nk && t4 < d) x = *reinterpret_cast<const float4 *>(vb + (int64_t)key * hs + t4);
-        const float xe[4] = {x.x * s_eff, x.y * s_eff, x.z * s_eff, x.w * s_eff};
-        const int slot = v_slot(j);
+    for (int idx = tid; idx < DV * 4; idx += 256) {
+        const int t = idx >> 2, c = idx & 3;
+        const int32_t key0 = 32 * tile + 16 * (c >> 1) + 4 * (c & 1);  // element e: key0 + 8 (e / 4) + e % 4 (v_slot)
+        float x[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t hb = bf16_rne_bits(xe[e]);
-            const uint32_t lb = bf16_rne_bits(xe[e] - __uint_as_float(hb));
-            const int off = v_row_slot(t4 + e, slot >> 3) + (slot & 7) * 2;
-            *reinterpret_cast<uint16_t *>(vhp + off) = (uint16_t)(hb >> 16);
-            *reinterpret_cast<uint16_t *>(vlp + off) = (uint16_t)(lb >> 16);
+        for (int e = 0; e < 8; ++e) {
+            const int32_t key = key0 + 8 * (e >> 2) + (e & 3);
+            x[e] = 0.0f;
+            if (key < nk && t < d) x[e] = vb[(int64_t)key * hs + t];
         }
+        uint32_t hb[8], lb[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float xe = x[e] * s_eff;
+            hb[e] = bf16_rne_bits(xe);
+            lb[e] = bf16_rne_bits(xe - __uint_as_float(hb[e]));
+        }
+        const int off = v_row_slot(t, c);
+        *reinterpret_cast<u32x4 *>(vhp + off) = u32x4{(hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3], (hb[4] >> 16) | hb[5], (hb[6] >> 16) | hb[7]};
+        *reinterpret_cast<u32x4 *>(vlp + off) = u32x4{(lb[0] >> 16) | lb[1], (lb[2] >> 16) | lb[3], (lb[4] >> 16) | lb[5], (lb[6] >> 16) | lb[7]};
     }
 }
 
