@@ -316,7 +316,9 @@ size_t dgq_codes_bytes(const dgq_groups_t *g, int64_t rows);
  * Quantized linear layer: grouped integer contraction and dequantization.
  *   acc[r,o,g] = sum_{j in g} code[r,j] * wq[o,j]                         (int32, exact)
  *   y[r,o]     = sw[o] * sum_g s[class(r),g] * float(acc[r,o,g]) + zb[class(r)][o]
- * (x_dq = s*(x_q) + z of Section 3.1 applied group by group; fp32 epilogue).
+ * (x_dq = s*(x_q) + z of Section 3.1 applied group by group; fp32 epilogue).  The sum runs over the
+ * groups in order, one fused multiply-add each, whatever the size of the call: a row's result has
+ * the same bits in any batch.
  *   codes, row_class: as written by dgq_quantize_act with the same g
  *   y: fp32 [rows, out_channels]
  *   acc_dump: NULL, or int32 [rows, out_channels, NG] receiving every group

@@ -236,7 +236,7 @@ int upload_tables(Groups *g) {
     const int32_t T = g->n_tab;
     g->n_chunks = (int32_t)g->perm.size() / kGranule;
     (void)hipGetDevice(&g->device);
-    std::vector<float> chunk_z((size_t)T * g->n_chunks), chunk_inv((size_t)T * g->n_chunks), chunk_s((size_t)T * g->n_chunks);
+    std::vector<float> chunk_z((size_t)T * g->n_chunks), chunk_inv((size_t)T * g->n_chunks);
     std::vector<float> zoff((size_t)T * NG);
     std::vector<int32_t> gchunk(NG + 1);
     for (int32_t k = 0; k <= NG; ++k) gchunk[k] = g->goff[k] / kGranule;
@@ -245,7 +245,6 @@ int upload_tables(Groups *g) {
             for (int32_t ch = gchunk[k]; ch < gchunk[k + 1]; ++ch) {
                 chunk_z[(size_t)p * g->n_chunks + ch] = g->z[p * NG + k];
                 chunk_inv[(size_t)p * g->n_chunks + ch] = g->inv_s[p * NG + k];
-                chunk_s[(size_t)p * g->n_chunks + ch] = g->s[p * NG + k];
             }
             zoff[(size_t)p * NG + k] =
                 (float)((double)g->z[p * NG + k] + (double)g->info.code_offset * (double)g->s[p * NG + k]);
@@ -270,6 +269,16 @@ int upload_tables(Groups *g) {
             for (int32_t ch = 0; ch < g->n_chunks; ++ch)
                 q_zi[(size_t)p * g->n_chunks + ch] = make_float2(chunk_z[(size_t)p * g->n_chunks + ch], chunk_inv[(size_t)p * g->n_chunks + ch]);
     }
+    const int32_t n_read = g->n_chunks + Groups::kReadAhead;
+    std::vector<float> chunk_s(2 * (size_t)n_read, 0.0f);
+    std::vector<uint32_t> chunk_ends(n_read, 0);
+    for (int32_t k = 0; k < NG; ++k)
+        for (int32_t ch = gchunk[k]; ch < gchunk[k + 1]; ++ch) {
+            chunk_s[ch] = g->s[k];
+            chunk_s[n_read + ch] = g->s[NG + k];
+            if (ch + 1 == gchunk[k + 1])
+                for (int32_t i = 0; i < 32 && i <= ch; ++i) chunk_ends[ch - i] |= 1u << i;
+        }
     TableBlock t;
     t.add(&g->d_perm, g->perm);
     if (g->q_steps) {
@@ -279,12 +288,13 @@ int upload_tables(Groups *g) {
     }
     t.add(&g->d_chunk_z, chunk_z);
     t.add(&g->d_chunk_inv, chunk_inv);
-    t.add(&g->d_chunk_s, chunk_s);
     t.add(&g->d_s, g->s);
     t.add(&g->d_z, g->z);
     t.add(&g->d_zoff, zoff);
     t.add(&g->d_taus, g->taus);
     t.add(&g->d_gchunk, gchunk);
+    t.add(&g->d_chunk_s, chunk_s);
+    t.add(&g->d_chunk_ends, chunk_ends);
     return t.upload(&g->d_tables);
 }
 

@@ -55,7 +55,10 @@ struct Groups {
     int32_t *d_perm = nullptr;     // [K'] original channel or -1
     float *d_chunk_z = nullptr;    // [n_tab][n_chunks]  offset of the chunk's group
     float *d_chunk_inv = nullptr;  // [n_tab][n_chunks]  1/s of the chunk's group
-    float *d_chunk_s = nullptr;    // [n_tab][n_chunks]  s of the chunk's group
+    // The small contraction kernel's tables, with kReadAhead entries behind the last chunk.
+    static constexpr int kReadAhead = 32;
+    float *d_chunk_s = nullptr;        // [2][n_chunks + kReadAhead]  scale of the chunk's group, classes 0 and 1
+    uint32_t *d_chunk_ends = nullptr;  // [n_chunks + kReadAhead]  bit i: the i-th chunk from this one on ends its group
     // The quantizer's tables per output dword (4 positions at 8 bit, 8 at 4 bit; 64 dwords a step, padded to
     // whole steps): byte offsets into a row of activations, two to a word, and the mask of real positions; then
     // (z, 1/s) of every chunk, class by class.  Null where offsets do not fit 16 bits.

@@ -42,13 +42,20 @@ struct ConvGather {
     const int8_t *fill = nullptr;
 };
 
-// The contraction for launches the chip is not full of (k2_direct.hip); arguments as for
-// launch_linear, cv for a gathered convolution.
-hipError_t launch_linear_direct(const Groups &g, const Weight &w, const int8_t *codes,
+// What the choice of a contraction kernel depends on.
+struct LinearShape {
+    int64_t rows, out_channels;
+    int32_t n_chunks, n_groups;
+    bool gated, conv, multi;  // gated epilogue, gathered taps, more than two pixel classes
+};
+
+// The contraction for launches the chip is not full of (k2_direct.hip): the block of outputs per wavefront (0: 16 x 16, 1: 16 x
+// 32, 2: 32 x 32; gated 32 x 16), or -1 where the ring kernel is the faster one.
+int direct_block(const LinearShape &s);
+// arguments as for launch_linear, cv for a gathered convolution
+hipError_t launch_linear_direct(int block, const Groups &g, const Weight &w, const int8_t *codes,
                                 const uint8_t *row_class, int64_t rows, float *y, int geglu,
                                 uint8_t *rq_cls, const ConvGather *cv, int32_t *acc_dump,
                                 hipStream_t st);
-// whether that kernel is the faster one for `rows` rows and `out_channels` channels
-bool linear_direct_pays(const Groups &g, int64_t rows, int64_t out_channels);
 
 }  // namespace dgq

@@ -842,8 +842,8 @@ hipError_t launch_linear_conv3x3(const Groups &g9, const Weight &w, const int8_t
     cv.chunks = g9.base_kp / kGranule;
     cv.copy_bytes = ((rows + rpb - 1) / rpb) * (int64_t)cv.chunks * 1024;
     cv.fill = reinterpret_cast<const int8_t *>(g9.d_fill_blocks);
-    if (linear_direct_pays(g9, rows, w.O))
-        return launch_linear_direct(g9, w, codes3, row_class, rows, y, 0, nullptr, &cv, nullptr, st);
+    if (const int b = direct_block({rows, w.O, g9.n_chunks, g9.info.n_groups, false, true, false}); b >= 0)
+        return launch_linear_direct(b, g9, w, codes3, row_class, rows, y, 0, nullptr, &cv, nullptr, st);
 #define DGQ_CONV(...)                                                                                               \
     return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv) \
               : launch_cfg<Cfg<4, __VA_ARGS__>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv)
@@ -863,8 +863,8 @@ hipError_t launch_linear(const Groups &g, const Weight &w, const int8_t *codes,
     const bool multi = g.n_tab > 2;  // more than two pixel classes (one channel group)
     if (multi && (geglu || acc_dump || g.info.n_groups != 1)) return hipErrorInvalidValue;
     if (geglu == 2 && (!w.d_rq_zi || !w.d_rq_keep || !rq_cls)) return hipErrorInvalidValue;
-    if (linear_direct_pays(g, rows, w.O))
-        return launch_linear_direct(g, w, codes, row_class, rows, y, geglu, rq_cls, nullptr, acc_dump, st);
+    if (const int b = direct_block({rows, w.O, g.n_chunks, g.info.n_groups, geglu != 0, false, multi}); b >= 0)
+        return launch_linear_direct(b, g, w, codes, row_class, rows, y, geglu, rq_cls, nullptr, acc_dump, st);
     int shape = ring_shape(rows, w.O);
     if (geglu) {
         // The gated epilogue needs two column blocks per wave.  With few chunks it is a third of a tile's life,
