@@ -358,10 +358,14 @@ def dgq_xattn_logq_intv(q, k, v_codes, v_params, key_bias, attn_bits: int = 4, o
         raise ValueError("k / v_codes have the wrong shape")
     if v_params.numel() != B * H * 2:
         raise ValueError("v_params must be [B, H, 2]")
+    if key_bias is not None and _dev(key_bias, torch.float32, "key_bias").numel() != nk:
+        raise ValueError("key_bias has the wrong shape")
     if out is None:
         out = torch.empty_like(q)
     if scale_out is None:
         scale_out = torch.empty(B, dtype=torch.float32, device=q.device)
+    if _dev(out, torch.float32, "out").numel() < q.numel() or _dev(scale_out, torch.float32, "scale_out").numel() < B:
+        raise ValueError("out / scale_out are too small")
     if acc_dump is not None:
         _dev(acc_dump, torch.int32, "acc_dump")
         if tuple(acc_dump.shape) != (B, N, H, d):
@@ -426,6 +430,8 @@ def dgq_quantize_value(v, v_bits: int = 8, v_hat=None, want_codes: bool = False,
     B, nk, H, d = v.shape
     if v_hat is None:
         v_hat = torch.empty_like(v)
+    if _dev(v_hat, torch.float32, "v_hat").numel() < v.numel():
+        raise ValueError("v_hat is too small")
     codes = torch.empty(v.shape, dtype=torch.uint8, device=v.device) if want_codes else None
     params = torch.empty((B, H, 2), dtype=torch.float32, device=v.device) if want_params else None
     _check(lib().dgq_quantize_value(_ptr(v), B, nk, H, d, v_bits, _ptr(v_hat),

@@ -126,6 +126,16 @@ bool shape_is(const at::Tensor &t, std::initializer_list<int64_t> s) {
     return t.sizes() == at::IntArrayRef(s.begin(), s.size());
 }
 
+// The C ABI sees no sizes: a tensor it would read or write past the end of is refused here.
+void holds(const at::Tensor &t, int64_t n, const char *name) {
+    if (t.numel() >= n) return;
+    PyErr_Format(PyExc_ValueError, "%s has %lld elements, the call needs %lld", name, (long long)t.numel(), (long long)n);
+    throw Raised();
+}
+void holds_if_given(PyObject *o, int64_t n, const char *name) {
+    if (given(o)) holds(THPVariable_Unpack(o), n, name);
+}
+
 template <class F>
 void enqueue(F &&call) {
     int rc;
@@ -301,6 +311,8 @@ PyObject *linear_conv3x3(Args a) {
     const at::Tensor &codes3 = tensor(a[2], at::kChar, "codes3"), &cls = tensor(a[3], at::kByte, "row_class");
     const int32_t B = integer32(a[4]), H = integer32(a[5]), W = integer32(a[6]);
     const int64_t rows = (int64_t)B * H * W, O = out_channels_of(a[1]);
+    holds(codes3, (int64_t)dgq_conv3x3_codes3_bytes(g9, B, H, W), "codes3");
+    holds(cls, rows, "row_class");
     const at::Tensor y = given(a[7]) ? tensor(a[7], at::kFloat, "y") : empty({rows, O}, at::kFloat, codes3);
     if (!shape_is(y, {rows, O})) raise_value("y has the wrong shape");
     void *st = stream_of(a[8]);
@@ -332,7 +344,9 @@ PyObject *xattn_logq(Args a) {
     if (kb && THPVariable_Unpack(a[3]).numel() != nk) raise_value("key_bias has the wrong shape");
     const int32_t bits = integer32(a[4]);
     const at::Tensor out = given(a[5]) ? tensor(a[5], at::kFloat, "out") : empty(q.sizes(), at::kFloat, q);
+    holds(out, q.numel(), "out");
     const at::Tensor scale = given(a[6]) ? tensor(a[6], at::kFloat, "scale_out") : empty({s.B}, at::kFloat, q);
+    holds(scale, s.B, "scale_out");
     uint8_t *dump = optional<uint8_t>(a[7], at::kByte, "codes_dump");
     if (dump && !shape_is(THPVariable_Unpack(a[7]), {s.B, s.H, s.N, nk - 1})) raise_value("codes_dump has the wrong shape");
     at::Tensor ws;
@@ -363,10 +377,15 @@ PyObject *xattn_logq_static(Args a) {
     if (nk > INT32_MAX || k.numel() != s.B * nk * s.H * s.d || v.numel() != k.numel())
         raise_value("k / v have the wrong size");
     const float *kb = optional<float>(a[3], at::kFloat, "key_bias");
+    holds_if_given(a[3], nk, "key_bias");
+    holds(sin, s.B, "scale_in");
     const int32_t bits = integer32(a[4]);
     const at::Tensor out = given(a[6]) ? tensor(a[6], at::kFloat, "out") : empty(q.sizes(), at::kFloat, q);
+    holds(out, q.numel(), "out");
     float *so = optional<float>(a[7], at::kFloat, "scale_out");
+    holds_if_given(a[7], s.B, "scale_out");
     uint8_t *dump = optional<uint8_t>(a[8], at::kByte, "codes_dump");
+    holds_if_given(a[8], s.B * s.H * s.N * (nk - 1), "codes_dump");
     void *st = stream_of(a[9]);
     const float *qp = pointer<float>(q), *kp = pointer<float>(k), *vp = pointer<float>(v), *ip = pointer<float>(sin);
     float *op = pointer<float>(out);
@@ -390,7 +409,9 @@ PyObject *selfattn_logq(Args a) {
         raise_value("q, k, v must share one shape [B,N,H,d] and scale_in have B entries");
     const int32_t bits = integer32(a[3]);
     const at::Tensor out = given(a[5]) ? tensor(a[5], at::kFloat, "out") : empty(q.sizes(), at::kFloat, q);
+    holds(out, q.numel(), "out");
     float *so = optional<float>(a[6], at::kFloat, "scale_out");
+    holds_if_given(a[6], s.B, "scale_out");
     uint8_t *dump = optional<uint8_t>(a[7], at::kByte, "codes_dump");
     if (dump && !shape_is(THPVariable_Unpack(a[7]), {s.B, s.H, s.N, s.N})) raise_value("codes_dump must be [B,H,N,N]");
     at::Tensor ws;
