@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void k_quantize_act(
     const uint32_t *__restrict__ q_off, const uint32_t *__restrict__ q_keep, const float2 *__restrict__ q_zi,
     const float *__restrict__ taus, int32_t n_tau, int8_t *__restrict__ codes,
     uint8_t *__restrict__ row_class, int32_t rows_per, int32_t conv_w, int64_t copy_bytes,
-    const uint32_t *__restrict__ fill32) {
+    const uint32_t *__restrict__ fill32, int64_t wg0) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     constexpr int kPer = BITS == 8 ? 4 : 8;
     constexpr int kDwPerChunk = 64 / kPer;
@@ -114,7 +114,8 @@ __global__ __launch_bounds__(256) void k_quantize_act(
     float2 *zi_tab = reinterpret_cast<float2 *>(lds_raw + (size_t)C * (W == 1 ? 16 : 8));  // more than two classes
     __shared__ float2 ext[2][W];  // the waves' extremes of a row
     const uint32_t c4n = (uint32_t)C >> 2;
-    const int64_t first = (W == 1 ? (int64_t)blockIdx.x * kWavesPerBlock + wave : (int64_t)blockIdx.x) * rows_per;
+    const int64_t wg = wg0 + blockIdx.x;  // wg0: the workgroups of the launches before this one
+    const int64_t first = (W == 1 ? wg * kWavesPerBlock + wave : wg) * rows_per;
     const int32_t n = first >= rows ? 0 : (int32_t)(rows - first < rows_per ? rows - first : rows_per);
 
     // An index past the end of the row is clamped to the last valid one, which re-reads a value that is
@@ -337,7 +338,7 @@ __global__ __launch_bounds__(256) void k_quantize_act_any(
 
 using Kern = void (*)(const float *, int64_t, int32_t, int32_t, int32_t, const uint32_t *, const uint32_t *,
                       const float2 *, const float *, int32_t, int8_t *, uint8_t *, int32_t, int32_t, int64_t,
-                      const uint32_t *);
+                      const uint32_t *, int64_t);
 struct Picked {
     Kern kern;
     LdsLimit *lim;
@@ -430,11 +431,15 @@ hipError_t launch_quantize_act(const Groups &g, const float *x, int64_t rows, in
         const hipError_t e = raise_lds_limit(*k.lim, reinterpret_cast<const void *>(k.kern), 128 * 1024);
         if (e != hipSuccess) return e;
     }
-    const int64_t per_wg = W == 1 ? (int64_t)kWavesPerBlock * per : per;
-    hipLaunchKernelGGL(k.kern, dim3((unsigned)((rows + per_wg - 1) / per_wg)), dim3(256), lds, st, x, rows, C,
-                       Kp / (a8 ? 4 : 8), g.n_chunks, g.d_q_off, g.d_q_keep, g.d_q_zi, g.d_taus, g.n_tab - 1, codes,
-                       row_class, per, conv_w, copy_bytes, fill32);
-    return hipGetLastError();
+    const int64_t per_wg = W == 1 ? (int64_t)kWavesPerBlock * per : per, wgs = (rows + per_wg - 1) / per_wg;
+    constexpr int64_t kMostWgs = 1 << 23;  // a grid holds less than 2^32 threads: a launch takes 2^27 rows, or 2^25 shared ones
+    for (int64_t wg0 = 0; wg0 < wgs; wg0 += kMostWgs) {
+        hipLaunchKernelGGL(k.kern, dim3((unsigned)(wgs - wg0 < kMostWgs ? wgs - wg0 : kMostWgs)), dim3(256), lds, st, x, rows, C,
+                           Kp / (a8 ? 4 : 8), g.n_chunks, g.d_q_off, g.d_q_keep, g.d_q_zi, g.d_taus, g.n_tab - 1, codes,
+                           row_class, per, conv_w, copy_bytes, fill32, wg0);
+        if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace dgq

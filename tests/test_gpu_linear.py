@@ -158,6 +158,24 @@ def test_quantizer_shapes(dgq, oracle, rows, C, ab):
     gg.free()
 
 
+def test_quantizer_beyond_one_grid(dgq):
+    """2^28 rows and a few: more workgroups than one grid holds (2^32 threads).  Codes and classes around the places
+    where a launch ends equal those of the same rows in a call of their own."""
+    import torch
+    rows, C = (1 << 28) + 40, 4
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((rows, C), generator=gen, device="cuda")
+    gg = dgq.dgq_calibrate_kmeans(x[:4096].contiguous(), 4, 1, dgq.DIM_CHANNEL)
+    codes, cls = dgq.dgq_quantize_act(gg, x, codes=torch.zeros(dgq.codes_shape(gg, rows), dtype=torch.int8, device="cuda"))
+    assert int(cls.max()) == 0
+    for first in (0, (1 << 27) - 64, (1 << 27), (1 << 28) - 64, rows // 32 * 32 - 32):
+        part = x[first:first + 128].contiguous()
+        n = part.shape[0]
+        want, _ = dgq.dgq_quantize_act(gg, part, codes=torch.zeros(dgq.codes_shape(gg, n), dtype=torch.int8, device="cuda"))
+        assert torch.equal(codes[first // 32:first // 32 + want.shape[0]], want), first
+    gg.free()
+
+
 @pytest.mark.parametrize("ab", [8, 4])
 @pytest.mark.parametrize("B,N,C,O,G", [
     (1, 31, 64, 31, 64),       # fewer chunks than wavefronts share them, one block short of full both ways
