@@ -349,7 +349,10 @@ Picked picked() {
     return {k_quantize_act<BITS, W, NV, NS, CONV>, &lim};
 }
 
-constexpr int kMostFloat4 = 8, kMostSteps = 10;  // of the widest four-wavefront kernel: 8192 channels
+// of the widest four-wavefront kernel: 8192 channels; 15360 positions at 8 bit (the padding of a 3 x 3 convolution's
+// nine times sixteen groups comes to 9072), 20480 at 4 bit
+constexpr int kMostFloat4 = 8;
+constexpr int most_steps(int bits) { return bits == 8 ? 15 : 10; }
 
 // The smallest kernel that holds nv float4 and ns output dwords per lane.
 template <int BITS, bool CONV>
@@ -370,7 +373,8 @@ Picked pick(int W, int nv, int ns) {
     DGQ_PICK(4, 5, 3);
     DGQ_PICK(4, 5, 6);
     DGQ_PICK(4, 8, 5);
-    DGQ_PICK(4, kMostFloat4, kMostSteps);
+    DGQ_PICK(4, kMostFloat4, 10);
+    if constexpr (BITS == 8 && !CONV) DGQ_PICK(4, kMostFloat4, most_steps(8));
 #undef DGQ_PICK
     return {nullptr, nullptr};
 }
@@ -381,7 +385,7 @@ bool vectorised(const Groups &g) { return g.info.channels % 4 == 0; }
 
 bool quantize_act_fits(const Groups &g) {
     if (!vectorised(g)) return sizeof(float) * (size_t)g.info.channels * kWavesPerBlock <= 160 * 1024;
-    return g.info.channels <= 4 * 256 * kMostFloat4 && g.q_steps <= 4 * kMostSteps;
+    return g.info.channels <= 4 * 256 * kMostFloat4 && g.q_steps <= 4 * most_steps(g.info.act_bits);
 }
 
 hipError_t launch_quantize_act(const Groups &g, const float *x, int64_t rows, int8_t *codes,

@@ -129,6 +129,28 @@ def test_large_map_tap_gathering(dgq, oracle, act_bits):
     _run(dgq, oracle, B, H, W, C, O, act_bits, "blocks", 78, sample=sample)
 
 
+@pytest.mark.parametrize("C", [500, 604])
+def test_unfolded_activations_of_many_padded_groups(dgq, C):
+    """The convolution's own handle quantizes unfolded activations: 9 C channels whose sixteen clusters per tap are each
+    padded to 64 positions (up to 13572 of them at 500 channels), with the codes that unfolding the map's codes gives."""
+    import torch
+    B, H, W = 1, 4, 8
+    run = di.linear_case(90 + C, B, H * W, C, 8)["X"]
+    # one octave of range per cluster, so that every cluster ends in padding
+    X = (run * np.exp2(np.arange(C) % 16).astype(np.float32)).astype(np.float32)
+    g = dgq.dgq_calibrate_kmeans(_dev(X), 8, 16, dgq.DIM_CHANNEL)
+    g9 = dgq.dgq_groups_for_conv3x3(g)
+    assert g9.info.k_padded > 10240
+    codes, _ = dgq.dgq_quantize_act(g, _dev(X))
+    want = dgq.dgq_conv3x3_codes(g9, codes, B, H, W, codes9=torch.zeros(dgq.codes_shape(g9, B * H * W), dtype=torch.int8, device="cuda"))
+    from oracle import im2col3x3
+    X9 = im2col3x3(X, B, H, W)
+    got, _ = dgq.dgq_quantize_act(g9, _dev(X9))
+    assert torch.equal(got, want)
+    g9.free()
+    g.free()
+
+
 def test_argument_errors(dgq):
     x = _dev(di.linear_case(1, 1, 64, 64, 8)["X"])
     g2 = dgq.dgq_calibrate_groups(x, 8, 64, 2)                  # two pixel classes
