@@ -4,9 +4,9 @@
  * These calls are not part of the method: they run the bare instruction the contraction is
  * built on and plain streaming kernels, so that a reported throughput can be set against what
  * the very box it was measured on delivers (sustained clocks under matrix load are well below
- * the clock the published peaks are quoted at).  Each call only enqueues one kernel on
+ * the clock the published peaks are quoted at).  Each of them only enqueues one kernel on
  * `stream` (a hipStream_t as void*); the caller times it.  Return: DGQ_OK or a negative
- * dgq_status (dgq.h).
+ * dgq_status (dgq.h).  The last call tells which kernel a launch takes.
  */
 #ifndef DGQ_PROBE_H
 #define DGQ_PROBE_H
@@ -45,6 +45,17 @@ int dgq_probe_stream(const void *src, void *dst, size_t bytes, int32_t mode, uin
  * What this reaches is the ceiling of a layer whose time is its fp32 output.
  */
 int dgq_probe_write_tiles(float *dst, int64_t rows, int32_t out_channels, void *stream);
+
+/*
+ * The kernel that a linear layer's launch takes (host only, for tests that mean to reach one of them):
+ *   rows, out_channels   of the call;  n_chunks = k_padded / 64 and n_groups of the group handle
+ *   kind   0 dgq_linear, 1 dgq_linear_geglu, 2 dgq_linear_geglu_requant, 3 dgq_linear with more than two
+ *          pixel classes, 4 dgq_linear_conv3x3
+ * Returns 0, 1, 2: one wavefront per block of 16 x 16, 16 x 32, 32 x 32 outputs (gated: 16 x 16 and 32 x 16, each
+ * with its gates); 10, 11, 12, 13: the LDS ring with tiles of 64 x 64, 64 x 128 behind four stages, 64 x 128
+ * behind three, 128 x 128.  DGQ_EINVAL for anything else.
+ */
+int dgq_probe_linear_kernel(int64_t rows, int32_t out_channels, int32_t n_chunks, int32_t n_groups, int32_t kind);
 
 #ifdef __cplusplus
 }

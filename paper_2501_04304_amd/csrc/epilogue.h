@@ -46,8 +46,12 @@ struct ConvGather {
 struct LinearShape {
     int64_t rows, out_channels;
     int32_t n_chunks, n_groups;
-    bool gated, conv, multi;  // gated epilogue, gathered taps, more than two pixel classes
+    int gated;         // 0, 1 gated epilogue, 2 gated and requantized
+    bool conv, multi;  // gathered taps, more than two pixel classes
 };
+
+// Tile of the ring kernel (k2_linear.hip): 0 64 x 64, 1 64 x 128 behind four stages, 2 64 x 128 behind three, 3 128 x 128.
+int ring_shape(const LinearShape &s);
 
 // The contraction for launches the chip is not full of (k2_direct.hip): the block of outputs per wavefront (0: 16 x 16, 1: 16 x
 // 32, 2: 32 x 32; gated 32 x 16), or -1 where the ring kernel is the faster one.

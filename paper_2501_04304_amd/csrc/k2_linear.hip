@@ -738,7 +738,7 @@ __global__ __launch_bounds__(CF::THREADS, CF::OCC) void k_linear(
             }
         };
         int32_t ch = 0;
-        if (!DUMP && STAGES <= 4) {
+        if (!DUMP) {
             // STAGES chunks per trip, every one of them in the steady state
             while (ch + 2 * STAGES - 2 < n_chunks) {
 #pragma unroll
@@ -817,13 +817,28 @@ hipError_t launch_cfg(const Groups &g, const Weight &w, const int8_t *codes,
 //   0  64 x 64, 4 waves of 32 x 32: less than 1.75 of the wider tiles per CU leave some CUs with twice the
 //      work of others (8192 x 320 -> 320: 8.0 -> 6.9 us, 8192 x 1280 -> 320: 14.3 -> 12.1, 4096 x 2560 -> 640:
 //      16.5 -> 14.6)
-static int ring_shape(int64_t rows, int32_t O) {
+int ring_shape(const LinearShape &s) {
 #ifdef DGQ_TUNING  // tuning builds only: a forced tile shape
-    if (const int v = tuning_value(kTuneLinearCfg); v >= 10) return v - 10;
+    if (const int v = tuning_value(kTuneLinearCfg); v >= 10) return s.gated && v < 12 ? 2 : v - 10;
 #endif
-    const int64_t t128 = ((rows + 127) / 128) * ((O + 127) / 128), t64x128 = ((rows + 63) / 64) * ((O + 127) / 128);
+    const int64_t tiles_o = (s.out_channels + 127) / 128;
+    const int64_t t128 = ((s.rows + 127) / 128) * tiles_o, t64x128 = ((s.rows + 63) / 64) * tiles_o;
     const int64_t rounds = (t128 + 511) / 512;
-    return t128 >= 512 && 5 * t128 >= 4 * 512 * rounds ? 3 : (t64x128 > 768 ? 2 : (t64x128 >= 448 ? 1 : 0));
+    int shape = t128 >= 512 && 5 * t128 >= 4 * 512 * rounds ? 3 : (t64x128 > 768 ? 2 : (t64x128 >= 448 ? 1 : 0));
+    if (s.gated) {
+        // The gated epilogue needs two column blocks per wave.  With few chunks it is a third of a tile's life,
+        // which more and smaller workgroups hide better (us, 64 x 128 / 128 x 128 tiles, requantizing: 8192 x 320 -> 2560
+        // 26 / 29, 65536 x 640 -> 5120 423 / 438, 16384 x 960 -> 7680 212 / 205; not requantizing: 5794 x 256 -> 2048 14.6 / 15.0,
+        // 65536 x 640 -> 5120 433 / 423).
+        if (shape < 2 || s.n_chunks < (s.gated == 2 ? 12 : 9)) shape = 2;
+    } else if (shape == 3 && !s.conv && tiles_o >= 32) {
+        // Wide outputs (32 column tiles and more: the first feed-forward projections) run 2-4 % fewer
+        // clocks on 64 x 128 tiles, four workgroups per CU, than on 128 x 128 (measured with the
+        // launch's clock counter on 65536 x 640 -> 5120 and 16384 x 1280 -> 10240, both code widths);
+        // every other large shape is 3-9 % slower there.
+        shape = 2;
+    }
+    return shape;
 }
 
 // The 3 x 3 convolution with its taps gathered by the loads (see ConvGather): `codes3` are the
@@ -842,12 +857,13 @@ hipError_t launch_linear_conv3x3(const Groups &g9, const Weight &w, const int8_t
     cv.chunks = g9.base_kp / kGranule;
     cv.copy_bytes = ((rows + rpb - 1) / rpb) * (int64_t)cv.chunks * 1024;
     cv.fill = reinterpret_cast<const int8_t *>(g9.d_fill_blocks);
-    if (const int b = direct_block({rows, w.O, g9.n_chunks, g9.info.n_groups, false, true, false}); b >= 0)
+    const LinearShape shape{rows, w.O, g9.n_chunks, g9.info.n_groups, 0, true, false};
+    if (const int b = direct_block(shape); b >= 0)
         return launch_linear_direct(b, g9, w, codes3, row_class, rows, y, 0, nullptr, &cv, nullptr, st);
 #define DGQ_CONV(...)                                                                                               \
     return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv) \
               : launch_cfg<Cfg<4, __VA_ARGS__>, false, 0, false, true>(g9, w, codes3, row_class, rows, y, nullptr, st, nullptr, &cv)
-    switch (ring_shape(rows, w.O)) {
+    switch (ring_shape(shape)) {
         case 0: DGQ_CONV(2, 2, 1, 1, 4, 4);
         case 1: DGQ_CONV(2, 2, 1, 2, 4, 4);
         case 2: DGQ_CONV(2, 2, 1, 2, 3, 4);
@@ -863,22 +879,10 @@ hipError_t launch_linear(const Groups &g, const Weight &w, const int8_t *codes,
     const bool multi = g.n_tab > 2;  // more than two pixel classes (one channel group)
     if (multi && (geglu || acc_dump || g.info.n_groups != 1)) return hipErrorInvalidValue;
     if (geglu == 2 && (!w.d_rq_zi || !w.d_rq_keep || !rq_cls)) return hipErrorInvalidValue;
-    if (const int b = direct_block({rows, w.O, g.n_chunks, g.info.n_groups, geglu != 0, false, multi}); b >= 0)
+    const LinearShape call{rows, w.O, g.n_chunks, g.info.n_groups, geglu, false, multi};
+    if (const int b = direct_block(call); b >= 0)
         return launch_linear_direct(b, g, w, codes, row_class, rows, y, geglu, rq_cls, nullptr, acc_dump, st);
-    int shape = ring_shape(rows, w.O);
-    if (geglu) {
-        // The gated epilogue needs two column blocks per wave.  With few chunks it is a third of a tile's life,
-        // which more and smaller workgroups hide better (us, 64 x 128 / 128 x 128 tiles, requantizing: 8192 x 320 -> 2560
-        // 26 / 29, 65536 x 640 -> 5120 423 / 438, 16384 x 960 -> 7680 212 / 205; not requantizing: 5794 x 256 -> 2048 14.6 / 15.0,
-        // 65536 x 640 -> 5120 433 / 423).
-        if (shape < 2 || g.n_chunks < (geglu == 2 ? 12 : 9)) shape = 2;
-    } else if (shape == 3 && (w.O + 127) / 128 >= 32) {
-        // Wide outputs (32 column tiles and more: the first feed-forward projections) run 2-4 % fewer
-        // clocks on 64 x 128 tiles, four workgroups per CU, than on 128 x 128 (measured with the
-        // launch's clock counter on 65536 x 640 -> 5120 and 16384 x 1280 -> 10240, both code widths);
-        // every other large shape is 3-9 % slower there.
-        shape = 2;
-    }
+    const int shape = ring_shape(call);
 #define DGQ_GATED(MODE, ...)                                                                                        \
     return a8 ? launch_cfg<Cfg<8, __VA_ARGS__>, false, MODE>(g, w, codes, row_class, rows, y, nullptr, st, rq_cls)    \
               : launch_cfg<Cfg<4, __VA_ARGS__>, false, MODE>(g, w, codes, row_class, rows, y, nullptr, st, rq_cls)

@@ -2,6 +2,7 @@
 // kernels (see include/dgq_probe.h).  Not part of the method.
 #include "dgq_internal.h"
 #include "dgq_probe.h"
+#include "epilogue.h"
 
 namespace dgq {
 namespace {
@@ -131,6 +132,16 @@ int dgq_probe_write_tiles(float *dst, int64_t rows, int32_t out_channels, void *
                        static_cast<hipStream_t>(stream), dst, (int64_t)out_channels * 4, tiles_o);
     DGQ_HIP(hipGetLastError());
     return DGQ_OK;
+}
+
+int dgq_probe_linear_kernel(int64_t rows, int32_t out_channels, int32_t n_chunks, int32_t n_groups, int32_t kind) {
+    if (rows < 1 || out_channels < 1 || n_chunks < 1 || n_groups < 1 || kind < 0 || kind > 4) {
+        set_error("dgq_probe_linear_kernel: not a launch");
+        return DGQ_EINVAL;
+    }
+    const LinearShape s{rows, out_channels, n_chunks, n_groups, kind == 1 || kind == 2 ? kind : 0, kind == 4, kind == 3};
+    const int block = direct_block(s);
+    return block >= 0 ? block : 10 + ring_shape(s);
 }
 
 }  // extern "C"

@@ -57,6 +57,20 @@ def codes_to_q(codes_np, act_bits, kp, rows):
     return q.reshape(packed.shape[0], kp)
 
 
+PLAIN, GATED, REQUANT, CLASSES, CONV = range(5)  # kinds of launch for kernel_of
+
+
+def kernel_of(rows, out_channels, kp, n_groups, kind):
+    """The kernel a linear layer's launch takes (include/dgq_probe.h): 0, 1, 2 a block of 16 x 16, 16 x 32, 32 x 32
+    per wavefront; 10 .. 13 the LDS ring with 64 x 64, 64 x 128 (four stages), 64 x 128 and 128 x 128 tiles."""
+    import ctypes
+
+    import paper_2501_04304_amd as dgq
+    f = dgq.lib().dgq_probe_linear_kernel
+    f.argtypes = [ctypes.c_int64] + [ctypes.c_int32] * 4
+    return f(rows, out_channels, kp // 64, n_groups, kind)
+
+
 def assert_close_fp32(got, ref, what=""):
     """The fp32 tolerance of the build: max|err| <= 1e-4 * max|ref|."""
     got = np.asarray(got, np.float64)

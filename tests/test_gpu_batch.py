@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import dgq_inputs as di
+from support import CLASSES, CONV, GATED, PLAIN, REQUANT, kernel_of
 
 pytestmark = pytest.mark.gpu
 
@@ -30,6 +31,11 @@ def _same_bits(few, many):
     assert torch.equal(few.view(torch.int32), many[:few.shape[0]].view(torch.int32))
 
 
+def _two_kernels(g, few, many, out_channels, kind):
+    a, b = (kernel_of(r, out_channels, g.info.k_padded, g.info.n_groups, kind) for r in (few, many))
+    assert a < 10 <= b
+
+
 def _calibrate(dgq, x, kind, ab):
     if kind == "channel":
         return dgq.dgq_calibrate_kmeans(x, ab, 16, dgq.DIM_CHANNEL)
@@ -52,6 +58,7 @@ def test_linear(dgq, kind, C, ab):
     run = di.linear_case(40 + C, 2, MANY // 2, C, 1280)
     x = _dev(run["X"])
     g = _calibrate(dgq, x, kind, ab)
+    _two_kernels(g, FEW, MANY, 1280, CLASSES if kind == "pixel" else PLAIN)
     bias = _dev(np.random.default_rng(C).standard_normal(1280).astype(np.float32))
     w = dgq.dgq_pack_weight(g, _dev(run["W"]), bias, 8)
     few = dgq.dgq_linear(g, w, *dgq.dgq_quantize_act(g, x[:FEW]))
@@ -77,11 +84,13 @@ def test_gated(dgq, kind, C, ab):
     run = di.linear_case(50 + C, 2, MANY // 2, C, 2560)
     x = _dev(run["X"])
     g = _calibrate(dgq, x, kind, ab)
+    _two_kernels(g, FEW, MANY, 2560, GATED)
     w = dgq.dgq_pack_weight(g, _dev(run["W"]), None, 8)
     few = dgq.dgq_linear_geglu(g, w, *dgq.dgq_quantize_act(g, x[:FEW]))
     many = dgq.dgq_linear_geglu(g, w, *dgq.dgq_quantize_act(g, x))
     _same_bits(few, many)
     g2 = dgq.dgq_calibrate_groups(many[:2048].contiguous(), ab, 128, 1)
+    _two_kernels(g, FEW, MANY, 2 * g2.info.k_padded, REQUANT)
     w2 = dgq.dgq_pack_weight_gated_for(g, g2, _dev(run["W"]), None, 8)
     codes_few, _ = dgq.dgq_linear_geglu_requant(g, w2, *dgq.dgq_quantize_act(g, x[:FEW]), g2)
     codes_many, _ = dgq.dgq_linear_geglu_requant(g, w2, *dgq.dgq_quantize_act(g, x), g2)
@@ -99,6 +108,7 @@ def test_convolution(dgq, kind, C, ab):
     x = _dev(run["X"])
     g = dgq.dgq_calibrate_kmeans(x, ab, 8, dgq.DIM_CHANNEL) if kind == "channel" else dgq.dgq_calibrate_groups(x, ab, 64, 1)
     g9 = dgq.dgq_groups_for_conv3x3(g)
+    _two_kernels(g9, H * W, B * H * W, O, CONV)
     k = np.random.default_rng(C).standard_normal((O, 9 * C)).astype(np.float32) * np.float32(0.02)
     w = dgq.dgq_pack_weight(g9, _dev(k), None, 8)
     out = []

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import dgq_inputs as di
-from support import assert_close_fp32, codes_to_q
+from support import CONV, assert_close_fp32, codes_to_q, kernel_of
 
 pytestmark = pytest.mark.gpu
 
@@ -37,6 +37,9 @@ def _run(dgq, oracle, B, H, W, C, O, act_bits, kind, seed, sample=None, check_ac
     if kind == "kmeans":
         og = oracle.calibrate_kmeans(cal["X"], act_bits, 8, 0)
         g = dgq.dgq_calibrate_kmeans(_dev(cal["X"]), act_bits, 8, dgq.DIM_CHANNEL)
+    elif kind == "one":  # a single group
+        og = oracle.calibrate_kmeans(cal["X"], act_bits, 1, 0)
+        g = dgq.dgq_calibrate_kmeans(_dev(cal["X"]), act_bits, 1, dgq.DIM_CHANNEL)
     else:
         og = oracle.calibrate(cal["X"], act_bits, 64, 1)
         g = dgq.dgq_calibrate_groups(_dev(cal["X"]), act_bits, 64, 1)
@@ -89,11 +92,14 @@ def _run(dgq, oracle, B, H, W, C, O, act_bits, kind, seed, sample=None, check_ac
         assert np.array_equal(dump.cpu().numpy()[sel], oacc)
     for hnd in (wt, g9, g):
         hnd.free()
+    return og9
 
 
 @pytest.mark.parametrize("kind", ["kmeans", "blocks"])
 @pytest.mark.parametrize("act_bits", [8, 4])
 @pytest.mark.parametrize("B,H,W,C,O", [
+    (1, 4, 32, 768, 24),    # the quantizer shares a row among four wavefronts (at most 1024 pixels, 768 channels)
+    (2, 3, 32, 1284, 24),
     (2, 9, 7, 72, 40),      # pixels not a multiple of the 16 / 32-row code blocks
     (1, 16, 16, 128, 128),
     (2, 6, 32, 72, 40),     # width of one or two code blocks, a ragged last row tile
@@ -116,17 +122,30 @@ def test_resnet_block_shape_sampled(dgq, oracle):
     _run(dgq, oracle, B, H, W, C, O, 8, "kmeans", 77, sample=sample)
 
 
+# B, H, W, C, O, grouping and the kernel that gathers the taps
+GATHERED = [
+    (1, 8, 32, 128, 72, "blocks", 0),
+    (1, 15, 64, 128, 520, "blocks", 1),
+    (2, 31, 64, 320, 330, "blocks", 2),
+    (2, 64, 64, 64, 330, "one", 10),
+    (2, 64, 64, 64, 600, "blocks", 11),
+    (2, 64, 64, 320, 1280, "blocks", 12),
+    (1, 127, 64, 64, 1650, "blocks", 13),   # ragged both ways
+    (2, 64, 64, 136, 1700, "blocks", 13),
+]
+
+
 @pytest.mark.parametrize("act_bits", [8, 4])
-def test_large_map_tap_gathering(dgq, oracle, act_bits):
-    """2 x 64 x 64 pixels, 320 -> 320 channels in blocks of 64: the launch takes the 128 x 128
-    tiles; the gathered and the unfolded convolution must agree on every output, the oracle
-    checks sampled pixels."""
-    B, H, W, C, O = 2, 64, 64, 320, 1280
+@pytest.mark.parametrize("B,H,W,C,O,kind,kernel", GATHERED)
+def test_large_map_tap_gathering(dgq, oracle, B, H, W, C, O, kind, kernel, act_bits):
+    """Every tile of the gathering contraction: the gathered and the unfolded convolution must agree on every output,
+    the oracle checks sampled pixels."""
     rng = np.random.default_rng(5)
     rows = B * H * W
     sample = np.unique(np.concatenate([rng.choice(rows, 10, replace=False),
-                                       [0, W - 1, W, H * W - 1, H * W, rows - W, rows - 1]]))
-    _run(dgq, oracle, B, H, W, C, O, act_bits, "blocks", 78, sample=sample)
+                                       [0, W - 1, W, H * W - 1, H * W % rows, rows - W, rows - 1]]))
+    og9 = _run(dgq, oracle, B, H, W, C, O, act_bits, kind, 78, sample=sample)
+    assert kernel_of(rows, O, og9.Kp, og9.NG, CONV) == kernel
 
 
 @pytest.mark.parametrize("C", [500, 604])

@@ -14,6 +14,7 @@ import numpy as np
 import pytest
 
 import dgq_inputs as di
+from support import GATED, kernel_of
 
 pytestmark = pytest.mark.gpu
 
@@ -79,23 +80,31 @@ def _run(dgq, oracle, B, N, C, O, G, act_bits, seed, sample_rows=None):
     assert (err2 <= lim2).all(), "chain: worst excess %.3e" % (err2 - lim2).max()
     wt.free()
     gg.free()
+    return og
+
+
+# B, N, C, O, G and the kernel that the launch takes, ragged rows and channels
+RAGGED = [
+    (2, 150, 328, 512, 64, 0),
+    (1, 77, 200, 256, 128, 0),
+    (2, 299, 384, 2048, 64, 2),
+    (2, 1111, 200, 1024, 64, 12),
+    (2, 2500, 136, 1792, 64, 12),
+    (2, 3750, 800, 1792, 64, 13),
+]
 
 
 @pytest.mark.parametrize("act_bits", [8, 4])
-@pytest.mark.parametrize("B,N,C,O,G", [
-    (2, 150, 328, 512, 64),     # 64 x 64 tiles, ragged rows and channels
-    (1, 77, 200, 256, 128),     # a single pair of column tiles
-    (2, 1111, 200, 1024, 64),   # 64 x 128 tiles, ragged rows
-    (2, 2500, 136, 1792, 64),   # 128 x 128 tiles, ragged rows
-])
-def test_small_and_ragged(dgq, oracle, B, N, C, O, G, act_bits):
+@pytest.mark.parametrize("B,N,C,O,G,kernel", RAGGED)
+def test_small_and_ragged(dgq, oracle, B, N, C, O, G, kernel, act_bits):
     M = B * N
     rows = None
     if M > 1000:
         rng = np.random.default_rng(O)
         rows = np.unique(np.concatenate([rng.choice(M, 30, replace=False),
                                          [0, 63, 64, 127, 128, M - 130, M - 65, M - 64, M - 1]]))
-    _run(dgq, oracle, B, N, C, O, G, act_bits, 700 + C + O, rows)
+    og = _run(dgq, oracle, B, N, C, O, G, act_bits, 700 + C + O, rows)
+    assert kernel_of(M, O, og.Kp, og.NG, GATED) == kernel
 
 
 @pytest.mark.parametrize("shape", [(16, 4096, 640, 5120), (16, 1024, 1280, 10240)])

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import dgq_inputs as di
-from support import assert_close_fp32, codes_to_q
+from support import CLASSES, assert_close_fp32, codes_to_q, kernel_of
 
 pytestmark = pytest.mark.gpu
 
@@ -96,6 +96,8 @@ SMALL = [
     (3, 129, 192, 257, 4, 8, 16, -1),  # the dimension chosen by D_d
     (2, 300, 640, 384, 8, 8, 2, 1),    # two pixel classes: the two-class kernels
     (2, 300, 640, 384, 8, 8, 1, 1),    # one cluster: the per-tensor quantizer
+    (1, 130, 768, 130, 8, 8, 8, 1),    # rows shared by four wavefronts of the quantizer, more than two classes
+    (1, 130, 1284, 72, 4, 8, 16, 1),
 ]
 
 
@@ -117,12 +119,21 @@ def test_small_layers(dgq, oracle, B, N, C, O, ab, wb, K, dim):
     _free(res)
 
 
+# B, N, C, O, K and the kernel that the launch takes, edges ragged both ways
+RAGGED = [
+    (2, 1111, 200, 1000, 8, 10),
+    (2, 1500, 200, 1290, 8, 11),
+    (2, 2500, 136, 1700, 16, 12),
+    (2, 3750, 136, 1700, 16, 13),
+    (2, 300, 200, 520, 8, 0),
+    (2, 450, 128, 470, 8, 1),
+    (2, 500, 72, 1010, 16, 2),
+]
+
+
 @pytest.mark.parametrize("ab", [8, 4])
-@pytest.mark.parametrize("B,N,C,O,K", [
-    (2, 1111, 200, 1000, 8),    # the 64 x 128 tile shape, ragged
-    (2, 2500, 136, 1700, 16),   # the 128 x 128 tile shape, ragged
-])
-def test_pixel_grouping_medium_and_large_tiles(dgq, oracle, B, N, C, O, K, ab):
+@pytest.mark.parametrize("B,N,C,O,K,kernel", RAGGED)
+def test_pixel_grouping_medium_and_large_tiles(dgq, oracle, B, N, C, O, K, kernel, ab):
     seed = 900 + C + O
     run = di.linear_case(seed, B, N, C, O)
     cal = di.linear_case(seed, B, N, C, O, calib=True)
@@ -132,7 +143,8 @@ def test_pixel_grouping_medium_and_large_tiles(dgq, oracle, B, N, C, O, K, ab):
     rows = np.unique(np.concatenate([rng.choice(M, 30, replace=False), run["rows_ot"][:6], edge]))
     bias = rng.standard_normal(O).astype(np.float32)
     res = _run(dgq, oracle, run["X"], cal["X"], run["W"], ab, 8, K, 1, bias=bias, sample_rows=rows)
-    assert res["og"].P == K
+    og = res["og"]
+    assert og.P == K and kernel_of(M, O, og.Kp, og.NG, CLASSES) == kernel
     _free(res)
 
 

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import dgq_inputs as di
-from support import assert_close_fp32, codes_to_q, gpu_groups_vs_oracle
+from support import PLAIN, assert_close_fp32, codes_to_q, gpu_groups_vs_oracle, kernel_of
 
 pytestmark = pytest.mark.gpu
 
@@ -113,24 +113,33 @@ def test_small_layers(dgq, oracle, B, N, C, O, G, ab, wb, P):
     _run_layer(dgq, oracle, run, cal, ab, wb, G, P, bias=bias)
 
 
+# B, N, C, O, G and the kernel that the launch takes, edges ragged both ways
+RAGGED = [
+    (2, 1111, 200, 1000, 64, 10),
+    (2, 1500, 200, 1290, 64, 11),
+    (2, 2500, 136, 1700, 64, 12),
+    (2, 3750, 136, 1700, 64, 13),
+    (1, 90, 200, 330, 64, 0),
+    (2, 500, 200, 470, 64, 1),
+    (2, 1250, 200, 470, 64, 2),
+]
+
+
 @pytest.mark.parametrize("ab", [8, 4])
-@pytest.mark.parametrize("B,N,C,O,G", [
-    (2, 1111, 200, 1000, 64),   # 35 x 8 tiles of 64 x 128: the medium tile shape, ragged
-    (2, 2500, 136, 1700, 64),   # 40 x 14 tiles of 128 x 128: the large tile shape, ragged
-])
-def test_ragged_medium_and_large_tiles(dgq, oracle, B, N, C, O, G, ab):
-    """Row, channel and output counts that are no multiple of anything, at sizes where
-    the launcher picks the 64 x 128 and the 128 x 128 tile (the small cases above all
-    take the 64 x 64 one); oracle on sampled rows that include both ends of the edge tiles."""
+@pytest.mark.parametrize("B,N,C,O,G,kernel", RAGGED)
+def test_ragged_medium_and_large_tiles(dgq, oracle, B, N, C, O, G, kernel, ab):
+    """Row, channel and output counts that are no multiple of anything, for every tile of the contraction (plain and
+    with the accumulator dump); oracle on sampled rows that include both ends of the edge tiles."""
     seed = 300 + C + O
     run = di.linear_case(seed, B, N, C, O)
     cal = di.linear_case(seed, B, N, C, O, calib=True)
     M = B * N
     rng = np.random.default_rng(seed)
     edge = [0, 63, 64, 127, 128, M - 130, M - 65, M - 64, M - 2, M - 1]
-    rows = np.unique(np.concatenate([rng.choice(M, 30, replace=False), run["rows_ot"][:6], edge]))
+    rows = np.unique(np.concatenate([rng.choice(M, 30, replace=False), run["rows_ot"][:6], np.clip(edge, 0, M - 1)]))
     bias = rng.standard_normal(O).astype(np.float32)
-    _run_layer(dgq, oracle, run, cal, ab, 8, G, 2, bias=bias, sample_rows=rows)
+    og = _run_layer(dgq, oracle, run, cal, ab, 8, G, 2, bias=bias, sample_rows=rows)
+    assert kernel_of(M, O, og.Kp, og.NG, PLAIN) == kernel
 
 
 @pytest.mark.parametrize("ab", [8, 4])
@@ -182,8 +191,8 @@ def test_quantizer_beyond_one_grid(dgq):
     (1, 32, 200, 32, 64),      # exactly one block
     (1, 33, 320, 36, 64),      # one row and one piece of channels into the next blocks
     (2, 40, 3072, 68, 128),    # a long chain of chunks, groups cut between wavefronts
-    (2, 1500, 320, 840, 64),   # the ring kernel's 64 x 64 tiles, ragged
-    (2, 1500, 640, 1290, 128),  # its 64 x 128 tiles behind four stages, ragged
+    (2, 1500, 320, 840, 64),
+    (2, 1500, 640, 1290, 128),
 ])
 def test_block_edges_of_the_small_and_medium_kernels(dgq, oracle, B, N, C, O, G, ab):
     seed = 500 + C + O

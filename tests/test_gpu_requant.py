@@ -20,7 +20,7 @@ import numpy as np
 import pytest
 
 import dgq_inputs as di
-from support import codes_to_q, gpu_groups_vs_oracle
+from support import REQUANT, codes_to_q, gpu_groups_vs_oracle, kernel_of
 
 pytestmark = pytest.mark.gpu
 
@@ -51,36 +51,43 @@ def _oracle_h(oracle, og1, X, W, bias):
     return oy, oracle.geglu(oy)
 
 
+def layers(oracle, B, N, C1, C2, G, act_bits, seed, next_kind, K=8, cal_rows=256, next_bits=8):
+    """The two layers' calibration by the oracle: (calibration rows, weights, bias, groups, calibration rows of the
+    following layer, its groups)."""
+    O = 2 * C2
+    cal = di.linear_case(seed, B, N, C1, O, calib=True)["X"]
+    W = di.linear_case(seed, B, N, C1, O)["W"] * np.float32(8.0)   # pre-activations of order one, so GELU bends
+    bias = (np.random.default_rng(seed).standard_normal(O) * 0.3).astype(np.float32)
+    og1 = oracle.calibrate(cal, act_bits, G, 2)
+    # the following layer is calibrated on the oracle's gated activation of calibration rows
+    rng = np.random.default_rng(seed + 1)
+    crow = np.sort(rng.choice(cal.shape[0], min(cal_rows, cal.shape[0]), replace=False))
+    _, hcal = _oracle_h(oracle, og1, cal[crow], W, bias)
+    og2 = oracle.calibrate_kmeans(hcal, next_bits, K, 0) if next_kind == "kmeans" else oracle.calibrate(hcal, next_bits, 64, 1)
+    return cal, W, bias, og1, hcal, og2
+
+
 def _run(dgq, oracle, B, N, C1, C2, G, act_bits, seed, next_kind, K=8, sample=None, cal_rows=256,
-         next_bits=8, run_rows=None):
+         next_bits=8, run_rows=None, kernel=None):
     """Layer 1: C1 -> 2 C2 (hybrid grid, two pixel classes, act_bits codes); layer 2 takes
     the C2 gated channels with 8-bit codes and channel groups only."""
     import torch
     O = 2 * C2
-    run = di.linear_case(seed, B, N, C1, O)
-    cal = di.linear_case(seed, B, N, C1, O, calib=True)
-    X, W = run["X"], run["W"] * np.float32(8.0)   # pre-activations of order one, so GELU bends
+    X = di.linear_case(seed, B, N, C1, O)["X"]
     if run_rows is not None:                        # a few rows of the same layer
         X = np.ascontiguousarray(X[:run_rows])
     rows = X.shape[0]
-    bias = (np.random.default_rng(seed).standard_normal(O) * 0.3).astype(np.float32)
     sel = np.arange(rows) if sample is None else np.asarray(sample)
 
-    og1 = oracle.calibrate(cal["X"], act_bits, G, 2)
-    g1 = dgq.dgq_calibrate_groups(_dev(cal["X"]), act_bits, G, 2)
+    cal, W, bias, og1, hcal, og2 = layers(oracle, B, N, C1, C2, G, act_bits, seed, next_kind, K, cal_rows, next_bits)
+    g1 = dgq.dgq_calibrate_groups(_dev(cal), act_bits, G, 2)
     gpu_groups_vs_oracle(g1, og1)
-
-    # the following layer is calibrated on the oracle's gated activation of calibration rows
-    rng = np.random.default_rng(seed + 1)
-    n_cal = cal["X"].shape[0]
-    crow = np.sort(rng.choice(n_cal, min(cal_rows, n_cal), replace=False))
-    _, hcal = _oracle_h(oracle, og1, cal["X"][crow], W, bias)
     if next_kind == "kmeans":
-        og2 = oracle.calibrate_kmeans(hcal, next_bits, K, 0)
         g2 = dgq.dgq_calibrate_kmeans(_dev(hcal), next_bits, K, dgq.DIM_CHANNEL)
     else:
-        og2 = oracle.calibrate(hcal, next_bits, 64, 1)
         g2 = dgq.dgq_calibrate_groups(_dev(hcal), next_bits, 64, 1)
+    if kernel is not None:
+        assert kernel_of(rows, 2 * og2.Kp, og1.Kp, og1.NG, REQUANT) == kernel
     assert g2.info.n_pixel_classes == 1 and g2.info.k_padded == og2.Kp
     t2 = g2.tables()
     assert np.array_equal(t2["perm"], og2.perm)
@@ -138,31 +145,43 @@ def _run(dgq, oracle, B, N, C1, C2, G, act_bits, seed, next_kind, K=8, sample=No
     return float(decided.mean()), float(diff.mean())
 
 
-@pytest.mark.parametrize("next_kind", ["kmeans", "blocks"])
-@pytest.mark.parametrize("B,N,C1,C2,G,ab", [
-    (2, 150, 328, 256, 64, 8),     # 64 x 64 tiles (half a chunk per tile), ragged rows
-    (1, 77, 200, 128, 128, 8),     # one column tile pair
-    (2, 1111, 200, 640, 64, 4),    # 64 x 128 tiles, 4-bit codes in, ragged rows
-    (2, 2500, 136, 896, 64, 8),    # 128 x 128 tiles, ragged rows
-])
-def test_small_and_ragged(dgq, oracle, B, N, C1, C2, G, ab, next_kind):
+KINDS = ["kmeans", "blocks"]
+# B, N, C1, C2, G, act_bits and the kernel that the launch takes, by the kind of the following layer (whose padded
+# positions are the launch's channels); ragged rows
+RAGGED = [
+    (2, 150, 328, 256, 64, 8, (0, 0)),
+    (1, 77, 200, 128, 128, 8, (0, 0)),
+    (2, 350, 328, 512, 64, 8, (2, 0)),
+    (2, 1111, 200, 640, 64, 4, (12, 12)),
+    (2, 2500, 136, 896, 64, 8, (12, 12)),
+    (2, 3750, 776, 896, 64, 4, (13, 13)),
+]
+RAGGED_TO_4_BIT = [
+    (2, 150, 328, 256, 64, 8, (0, 0)),
+    (2, 350, 328, 512, 64, 8, (2, 0)),
+    (2, 1111, 200, 640, 64, 4, (12, 12)),
+    (2, 2500, 136, 896, 64, 8, (12, 12)),
+    (2, 3750, 776, 896, 64, 8, (12, 13)),
+]
+
+
+@pytest.mark.parametrize("next_kind", KINDS)
+@pytest.mark.parametrize("B,N,C1,C2,G,ab,kernels", RAGGED)
+def test_small_and_ragged(dgq, oracle, B, N, C1, C2, G, ab, kernels, next_kind):
     M = B * N
     sample = None
     if M > 1000:
         rng = np.random.default_rng(C2)
         sample = np.unique(np.concatenate([rng.choice(M, 40, replace=False),
                                            [0, 15, 16, 63, 64, 127, 128, M - 130, M - 17, M - 16, M - 1]]))
-    decided, _ = _run(dgq, oracle, B, N, C1, C2, G, ab, 900 + C1 + C2, next_kind, sample=sample)
+    decided, _ = _run(dgq, oracle, B, N, C1, C2, G, ab, 900 + C1 + C2, next_kind, sample=sample,
+                      kernel=kernels[KINDS.index(next_kind)])
     assert decided > 0.9
 
 
-@pytest.mark.parametrize("next_kind", ["kmeans", "blocks"])
-@pytest.mark.parametrize("B,N,C1,C2,G,ab", [
-    (2, 150, 328, 256, 64, 8),
-    (2, 1111, 200, 640, 64, 4),
-    (2, 2500, 136, 896, 64, 8),
-])
-def test_four_bit_codes_for_the_following_layer(dgq, oracle, B, N, C1, C2, G, ab, next_kind):
+@pytest.mark.parametrize("next_kind", KINDS)
+@pytest.mark.parametrize("B,N,C1,C2,G,ab,kernels", RAGGED_TO_4_BIT)
+def test_four_bit_codes_for_the_following_layer(dgq, oracle, B, N, C1, C2, G, ab, kernels, next_kind):
     M = B * N
     sample = None
     if M > 1000:
@@ -170,7 +189,7 @@ def test_four_bit_codes_for_the_following_layer(dgq, oracle, B, N, C1, C2, G, ab
         sample = np.unique(np.concatenate([rng.choice(M, 40, replace=False),
                                            [0, 31, 32, 63, 64, 127, 128, M - 130, M - 33, M - 32, M - 1]]))
     decided, _ = _run(dgq, oracle, B, N, C1, C2, G, ab, 950 + C1 + C2, next_kind, sample=sample,
-                      next_bits=4)
+                      next_bits=4, kernel=kernels[KINDS.index(next_kind)])
     assert decided > 0.99
 
 
