@@ -826,11 +826,13 @@ int ring_shape(const LinearShape &s) {
     const int64_t rounds = (t128 + 511) / 512;
     int shape = t128 >= 512 && 5 * t128 >= 4 * 512 * rounds ? 3 : (t64x128 > 768 ? 2 : (t64x128 >= 448 ? 1 : 0));
     if (s.gated) {
-        // The gated epilogue needs two column blocks per wave.  With few chunks it is a third of a tile's life,
-        // which more and smaller workgroups hide better (us, 64 x 128 / 128 x 128 tiles, requantizing: 8192 x 320 -> 2560
-        // 26 / 29, 65536 x 640 -> 5120 423 / 438, 16384 x 960 -> 7680 212 / 205; not requantizing: 5794 x 256 -> 2048 14.6 / 15.0,
-        // 65536 x 640 -> 5120 433 / 423).
-        if (shape < 2 || s.n_chunks < (s.gated == 2 ? 12 : 9)) shape = 2;
+        // The gated epilogue needs two column blocks per wave.  More and smaller workgroups hide it, and the folds
+        // between, better; only a long loop with few folds has use for the fewer operand bytes of the large tile.  us, 64 x 128 / 128 x 128
+        // tiles in turn, 8-bit codes, groups of 128: 65536 x 640 -> 5120 (11 chunks) 416 / 434, 16384 x 960 -> 7680 (16) 220 / 232,
+        // 8192 x 1280 -> 2560 (21) 49.4 / 47.1, 8192 x 2560 -> 5120 (41) 167 / 157; groups of 64: 32768 x 1280 -> 5120 (21) 376 / 395;
+        // requantizing: 65536 x 640 -> 5120 410 / 431, 8192 x 2048 -> 2560 (33) 72.5 / 73.2, 8192 x 2560 -> 5120 (41) 166 / 161, groups
+        // of 64: 7500 x 2560 -> 1792 (41) 66 / 73.
+        if (shape < 2 || s.n_chunks < (s.gated == 2 ? 40 : 20) || 4 * s.n_groups > 3 * s.n_chunks) shape = 2;
     } else if (shape == 3 && !s.conv && tiles_o >= 32) {
         // Wide outputs (32 column tiles and more: the first feed-forward projections) run 2-4 % fewer
         // clocks on 64 x 128 tiles, four workgroups per CU, than on 128 x 128 (measured with the

@@ -90,7 +90,8 @@ RAGGED = [
     (2, 299, 384, 2048, 64, 2),
     (2, 1111, 200, 1024, 64, 12),
     (2, 2500, 136, 1792, 64, 12),
-    (2, 3750, 800, 1792, 64, 13),
+    (2, 3750, 800, 1792, 64, 12),
+    (2, 3750, 1280, 1792, 128, 13),
 ]
 
 

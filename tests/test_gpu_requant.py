@@ -154,14 +154,14 @@ RAGGED = [
     (2, 350, 328, 512, 64, 8, (2, 0)),
     (2, 1111, 200, 640, 64, 4, (12, 12)),
     (2, 2500, 136, 896, 64, 8, (12, 12)),
-    (2, 3750, 776, 896, 64, 4, (13, 13)),
+    (2, 3750, 2560, 896, 128, 4, (12, 13)),
 ]
 RAGGED_TO_4_BIT = [
     (2, 150, 328, 256, 64, 8, (0, 0)),
     (2, 350, 328, 512, 64, 8, (2, 0)),
     (2, 1111, 200, 640, 64, 4, (12, 12)),
     (2, 2500, 136, 896, 64, 8, (12, 12)),
-    (2, 3750, 776, 896, 64, 8, (12, 13)),
+    (2, 3750, 2560, 896, 128, 8, (12, 13)),
 ]
 
 
