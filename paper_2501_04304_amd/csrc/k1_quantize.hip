@@ -16,14 +16,15 @@
 // mask that clears padding positions of the packed word, (z, 1/s) for both classes, the place in the tiled
 // row -- stays in REGISTERS for all of the wavefront's rows, read once from tables prepared with the
 // handle: no table build and no barrier before the first row, a quarter less LDS traffic per position, and LDS holds
-// nothing but the rows.  A row of more than 1280 channels is shared by four wavefronts instead (two row
-// buffers and one barrier per row): the tables still fit, and a CU holds twelve wavefronts where one row
-// per wavefront left it four.  So are the rows of a launch with few of them.
+// nothing but the rows.  A row of more than 1280 channels (2560 with 4-bit codes, whose lanes take twice as many positions)
+// is shared by four wavefronts instead (two row buffers and one barrier per row): the tables still fit, and a
+// CU holds twelve wavefronts where one row per wavefront left it four.  So are longer rows of a launch with few of them.
 //
 // The loop over rows stores without conditions (a lane past the last output dword repeats that
 // dword): then the wait for the prefetched row is a wait for exactly that row, while with one conditional
 // store it becomes a wait for every store before it as well, a write round trip per row (the classes, too,
-// are kept and stored once per wavefront).  Measured against the kernel that built its tables in LDS and
+// are kept and stored once per wavefront).  The form that writes a convolution's shifted copies does not have this: which
+// copies a pixel goes to depends on its column, and its stores wait.  Measured against the kernel that built its tables in LDS and
 // stored conditionally, us: 154 x 768 4.1 -> 2.8, 512 x 1280 5.0 -> 3.2, 8192 x 320 7.5 -> 4.7, 2964 x 1280 7.0 -> 5.7,
 // 65536 x 640 41.5 -> 37.0 (5.8 TB/s), 16384 x 1280 24.1 -> 21.2, 16384 x 5120 8-bit 98.8 -> 75.3 (5.6 TB/s), 4-bit
 // 88.7 -> 72.3 (5.2 TB/s); a copy reaches 4.9 TB/s.
@@ -407,14 +408,16 @@ hipError_t launch_quantize_act(const Groups &g, const float *x, int64_t rows, in
                            g.n_chunks, g.d_perm, g.d_chunk_z, g.d_chunk_inv, g.d_taus, g.n_tab - 1, codes, row_class);
         return hipGetLastError();
     }
-    // One wavefront per row where its registers hold the tables (1280 channels at 8 bit, 2560 at 4 bit) and
-    // there are rows enough for the chip's wavefronts; otherwise four.  (us, one / four: 512 x 1280 3.6 / 3.2, 1024 x 640
-    // 3.0 / 3.7, 2964 x 1280 5.6 / 6.4, 16384 x 2560 8-bit not built / 39.8, 4-bit 35.6 / 39.9)
+    // One wavefront per row where its registers hold the tables (1280 channels at 8 bit, 2560 at 4 bit);
+    // otherwise four, and also where a row is longer than what the smallest kernels hold and all the workgroups
+    // are resident at once, three to a CU with room left (us, one / four: 8-bit 512 x 704 2.67 / 2.93, 512 x 768 3.03 / 2.90,
+    // 640 x 768 3.06 / 3.11, 512 x 1280 3.37 / 2.97, 704 x 1280 3.40 / 3.19, 768 x 1280 3.42 / 3.64, 2964 x 1280 5.6 / 6.4; 4-bit
+    // 512 x 768 2.80 / 3.03, 512 x 800 3.58 / 3.04, 704 x 2048 4.13 / 3.65, 768 x 2560 4.20 / 4.76, 16384 x 2560 35.6 / 39.9).
     auto wave_holds = [&] {
         const int nv = (C + 255) / 256, ns = g.q_steps;
         return (nv <= 5 && ns <= 8) || (!a8 && nv <= 10 && ns <= 6);
     };
-    const int W = wave_holds() && !(rows <= 1024 && C >= 768) ? 1 : 4;
+    const int W = wave_holds() && !(rows <= 704 && C >= (a8 ? 768 : 772)) ? 1 : 4;
     const int nv = (C + 256 * W - 1) / (256 * W), ns = (g.q_steps + W - 1) / W;
     // Rows per wavefront (or per workgroup of four sharing them): as many as the chip's resident wavefronts leave
     // over, which spares table reads, but at most four (more leaves the last ones uneven).  A wavefront with

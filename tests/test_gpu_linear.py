@@ -145,8 +145,8 @@ def test_ragged_medium_and_large_tiles(dgq, oracle, B, N, C, O, G, kernel, ab):
 @pytest.mark.parametrize("ab", [8, 4])
 @pytest.mark.parametrize("rows,C", [
     (5, 256), (4099, 260),    # one wavefront per row; one and two rows each, a whole and a barely begun register
-    (1025, 1280), (1024, 1280), (7, 764),  # either side of the row count that shares a row among four wavefronts
-    (1030, 1284), (1030, 2560), (1030, 2564),  # and of the widths that do (8-bit and 4-bit codes)
+    (705, 1280), (704, 1280), (7, 764), (7, 768), (7, 772),  # either side of the row count and of the widths that share
+    (1025, 1280), (1024, 1280), (1030, 1284), (1030, 2560), (1030, 2564),  # a row among four wavefronts, both code widths
     (3, 5120), (2051, 5120), (6, 7168),
 ])
 def test_quantizer_shapes(dgq, oracle, rows, C, ab):

@@ -146,28 +146,26 @@ def _run(dgq, oracle, B, N, C1, C2, G, act_bits, seed, next_kind, K=8, sample=No
 
 
 KINDS = ["kmeans", "blocks"]
-# B, N, C1, C2, G, act_bits and the kernel that the launch takes, by the kind of the following layer (whose padded
-# positions are the launch's channels); ragged rows
-RAGGED = [
+# B, N, C1, C2, G, act_bits, the kind of the following layer (whose padded positions are the launch's channels) and the
+# kernel that the launch takes; ragged rows
+RAGGED = [(*s, kind, kernel) for *s, kernels in [
     (2, 150, 328, 256, 64, 8, (0, 0)),
     (1, 77, 200, 128, 128, 8, (0, 0)),
     (2, 350, 328, 512, 64, 8, (2, 0)),
     (2, 1111, 200, 640, 64, 4, (12, 12)),
     (2, 2500, 136, 896, 64, 8, (12, 12)),
     (2, 3750, 2560, 896, 128, 4, (12, 13)),
-]
-RAGGED_TO_4_BIT = [
+] for kind, kernel in zip(KINDS, kernels)]
+RAGGED_TO_4_BIT = [(*s, kind, kernel) for *s, kernels in [
     (2, 150, 328, 256, 64, 8, (0, 0)),
     (2, 350, 328, 512, 64, 8, (2, 0)),
     (2, 1111, 200, 640, 64, 4, (12, 12)),
     (2, 2500, 136, 896, 64, 8, (12, 12)),
-    (2, 3750, 2560, 896, 128, 8, (12, 13)),
-]
+] for kind, kernel in zip(KINDS, kernels)] + [(2, 3750, 2560, 896, 128, 8, "blocks", 13)]
 
 
-@pytest.mark.parametrize("next_kind", KINDS)
-@pytest.mark.parametrize("B,N,C1,C2,G,ab,kernels", RAGGED)
-def test_small_and_ragged(dgq, oracle, B, N, C1, C2, G, ab, kernels, next_kind):
+@pytest.mark.parametrize("B,N,C1,C2,G,ab,next_kind,kernel", RAGGED)
+def test_small_and_ragged(dgq, oracle, B, N, C1, C2, G, ab, next_kind, kernel):
     M = B * N
     sample = None
     if M > 1000:
@@ -175,13 +173,12 @@ def test_small_and_ragged(dgq, oracle, B, N, C1, C2, G, ab, kernels, next_kind):
         sample = np.unique(np.concatenate([rng.choice(M, 40, replace=False),
                                            [0, 15, 16, 63, 64, 127, 128, M - 130, M - 17, M - 16, M - 1]]))
     decided, _ = _run(dgq, oracle, B, N, C1, C2, G, ab, 900 + C1 + C2, next_kind, sample=sample,
-                      kernel=kernels[KINDS.index(next_kind)])
+                      kernel=kernel)
     assert decided > 0.9
 
 
-@pytest.mark.parametrize("next_kind", KINDS)
-@pytest.mark.parametrize("B,N,C1,C2,G,ab,kernels", RAGGED_TO_4_BIT)
-def test_four_bit_codes_for_the_following_layer(dgq, oracle, B, N, C1, C2, G, ab, kernels, next_kind):
+@pytest.mark.parametrize("B,N,C1,C2,G,ab,next_kind,kernel", RAGGED_TO_4_BIT)
+def test_four_bit_codes_for_the_following_layer(dgq, oracle, B, N, C1, C2, G, ab, next_kind, kernel):
     M = B * N
     sample = None
     if M > 1000:
@@ -189,7 +186,7 @@ def test_four_bit_codes_for_the_following_layer(dgq, oracle, B, N, C1, C2, G, ab
         sample = np.unique(np.concatenate([rng.choice(M, 40, replace=False),
                                            [0, 31, 32, 63, 64, 127, 128, M - 130, M - 33, M - 32, M - 1]]))
     decided, _ = _run(dgq, oracle, B, N, C1, C2, G, ab, 950 + C1 + C2, next_kind, sample=sample,
-                      next_bits=4, kernel=kernels[KINDS.index(next_kind)])
+                      next_bits=4, kernel=kernel)
     assert decided > 0.99
 
 

@@ -38,11 +38,10 @@ def test_gated(oracle, ab):
 
 @pytest.mark.parametrize("bits,shapes,seed", [(8, test_gpu_requant.RAGGED, 900), (4, test_gpu_requant.RAGGED_TO_4_BIT, 950)])
 def test_requantized(oracle, bits, shapes, seed):
-    for B, N, C1, C2, G, ab, kernels in shapes:
-        for kind, kernel in zip(test_gpu_requant.KINDS, kernels):
-            _, _, _, g, _, g2 = test_gpu_requant.layers(oracle, B, N, C1, C2, G, ab, seed + C1 + C2, kind, next_bits=bits)
-            assert kernel_of(B * N, 2 * g2.Kp, g.Kp, g.NG, REQUANT) == kernel, (B, N, C1, C2, kind)
-    assert {k for s in shapes for k in s[-1]} == SPLIT
+    for B, N, C1, C2, G, ab, kind, kernel in shapes:
+        _, _, _, g, _, g2 = test_gpu_requant.layers(oracle, B, N, C1, C2, G, ab, seed + C1 + C2, kind, next_bits=bits)
+        assert kernel_of(B * N, 2 * g2.Kp, g.Kp, g.NG, REQUANT) == kernel, (B, N, C1, C2, kind)
+    assert {s[-1] for s in shapes} == SPLIT
 
 
 @pytest.mark.parametrize("ab", [8, 4])
