@@ -48,10 +48,10 @@ def _calibrate(dgq, x, kind, ab):
 @pytest.mark.parametrize("kind,C", [
     (64, 320),          # every chunk a group
     (128, 768),         # groups of two chunks and a shorter one
-    (256, 1288),        # groups as long as a round
+    (256, 1288),        # groups of four chunks
     ("channel", 1280),  # groups of any length
     ("pixel", 1280),    # one group, sixteen classes
-    (128, 64), (128, 200),  # fewer chunks than wavefronts share, one more than that
+    (128, 64), (128, 200),  # about as many chunks as are read ahead
 ])
 def test_linear(dgq, kind, C, ab):
     import torch
