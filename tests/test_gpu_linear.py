@@ -146,7 +146,7 @@ def test_ragged_medium_and_large_tiles(dgq, oracle, B, N, C, O, G, kernel, ab):
 @pytest.mark.parametrize("rows,C", [
     (5, 256), (4099, 260),    # one wavefront per row; one and two rows each, a whole and a barely begun register
     (705, 1280), (704, 1280), (7, 764), (7, 768), (7, 772),  # either side of the row count and of the widths that share
-    (1025, 1280), (1024, 1280), (1030, 1284), (1030, 2560), (1030, 2564),  # a row among four wavefronts, both code widths
+    (1025, 1280), (1024, 1280), (1030, 1284), (1030, 2560), (1030, 2564),  # wide rows: one wavefront, or four from 1284 (8-bit) or 2564 channels
     (3, 5120), (2051, 5120), (6, 7168),
 ])
 def test_quantizer_shapes(dgq, oracle, rows, C, ab):
@@ -187,10 +187,10 @@ def test_quantizer_beyond_one_grid(dgq):
 
 @pytest.mark.parametrize("ab", [8, 4])
 @pytest.mark.parametrize("B,N,C,O,G", [
-    (1, 31, 64, 31, 64),       # fewer chunks than wavefronts share them, one block short of full both ways
+    (1, 31, 64, 31, 64),       # fewer chunks than are read ahead, one block short of full both ways
     (1, 32, 200, 32, 64),      # exactly one block
     (1, 33, 320, 36, 64),      # one row and one piece of channels into the next blocks
-    (2, 40, 3072, 68, 128),    # a long chain of chunks, groups cut between wavefronts
+    (2, 40, 3072, 68, 128),    # a long chain of chunks
     (2, 1500, 320, 840, 64),
     (2, 1500, 640, 1290, 128),
 ])
