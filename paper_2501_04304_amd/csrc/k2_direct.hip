@@ -426,8 +426,8 @@ hipError_t launch_kind(const Call &c) {
 
 // Which block, or -1 where the ring kernel is the faster one.  For T blocks of 32 x 32 outputs, n chunks and g groups
 // the times in ns, fitted to a sweep over 19 .. 16384 rows, 64 .. 11520 channels and 128 .. 10240 outputs (linear
-// layers, gated ones and convolutions, both code widths, 200 shapes: the rule's choice is 0.3 % off the better of the
-// two on average, 20 % at most): this kernel takes its chain of chunks (and a branch per group where groups are
+// layers, gated ones and convolutions, both code widths, 280 launches: the rule's choice is 0.5 % off the fastest of all
+// blocks and tiles on average, 20 % at most): this kernel takes its chain of chunks (and a branch per group where groups are
 // longer than a chunk) or its traffic, whichever is longer, and a third of the other; the ring kernel takes 1.3 us
 // more to start, then its chain of chunks and folds or its throughput per 64 x 64 tile.
 // The blocks by T: 16 x 16 up to 384, i.e. 1.5 wavefronts per SIMD (512 x 2560 -> 640, T = 320: 6.8 us against 7.8 with 16 x 32;
