@@ -659,24 +659,48 @@ bool mfma_shape(int32_t d, int32_t nk) {
 // with the 16-byte slots of every row XOR-permuted by row bits, so that the 16-byte fragment
 // reads of 32 consecutive rows spread over all banks.  The second kernel gives each of its
 // eight wavefronts 32 queries (their fp16 pieces stay in registers) and sweeps the key tiles
-// twice through a three-stage LDS ring filled by direct-to-LDS loads of 1 KiB (the tile
-// image is copied verbatim): sweep A takes the running maximum and sum of 2^(S - max) for
-// lse2, sweep B recomputes S^T bit-identically, forms the codes from log2 s + lse2 - S as
+// twice through a four-stage LDS ring (three for the widest heads) filled by direct-to-LDS loads of 1 KiB (the tile
+// image is copied verbatim): sweep A takes the sum of 2^(S - ref), ref the maximum of the
+// first tile, for lse2, sweep B recomputes S^T bit-identically, forms the codes from log2 s + lse2 - S as
 // above and accumulates Out^T = V^T P^T.  A code depends on the row's full sum, so one
 // sweep cannot do both.  (Read straight from memory by every wavefront, the fragments cost
 // 24 KB of cache traffic per wavefront and tile pair and the texture path, not the matrix
 // cores, set the pace: 5.8 ms on 16 x 10 x 4096 x 64.)
-template <int KS_>
+//
+// What bounds it: the matrix cores, and the clock they leave (1.4 - 1.7 GHz).  So padding is kept out of the
+// products.  A head of an odd number of eights of dims (8, 24, 40, 56, 72) has half a 16-dim step left: its
+// three products are two, [Kh Kh] [Qh Ql]^T and [Kl 0] [Qh 0]^T, the lane halves reading the same eight dims
+// of K.  And where the high and the low part of V^T, stacked, fill fewer 32-row blocks than each by itself,
+// they are stacked (row t high, row d + t low, summed at the end; d % 8 = 0 puts the two into the same lane).
+// 40 dims: 8 + 8 + 6 instructions per 32 x 32 tile where 9 + 9 + 8 were.
+// And the products of tile kt + 1 are issued among the exponentials or codes of tile kt, from which they are
+// independent: at 2 x 8 x 4096 x 40 the launch is one workgroup per CU, two wavefronts per SIMD, which a
+// barrier per tile keeps in phase, so that nobody else's vector work would fill the matrix instructions' time.
+// Measured, the call before and now, us: 2 x 8 x 4096 x 40 211 -> 193; in another run (B x N x H x d)
+// 8 x 1024 x 10 x 40 99.9 -> 91.3, 2 x 2100 x 8 x 48 105 -> 98, 2 x 1024 x 8 x 80 77.7 -> 74.4,
+// 16 x 4096 x 10 x 64 2310 -> 2271.
+template <int KS_, bool HALF_ = false>
 struct SCfg {
     static constexpr int KS = KS_;
+    static constexpr bool HALF = HALF_;       // the last 16-dim step holds eight dims
     static constexpr int DB = (KS + 1) / 2;   // 32-wide blocks of output dims
     static constexpr int DV = 32 * DB;
+    // up to 80 dims a kernel has one head width, d = 8 * D8; above, ten steps serve every width
+    static constexpr bool EXACT = KS <= 5;
+    static constexpr int D8 = 2 * KS - (HALF ? 1 : 0);
+    static constexpr bool STACK = EXACT && (D8 + 1) / 2 < 2 * DB;
+    static constexpr int NV = STACK ? (D8 + 1) / 2 : 2 * DB;  // 32-row blocks of V^T, high and low part
+    static constexpr int NO = STACK ? NV : DB;                // blocks they are accumulated in
+    static constexpr int VDIMS = STACK ? 8 * D8 : DV;         // rows of the high part, padding included
     static constexpr int PITCH = 128 * ((KS + 3) / 4);  // bytes per K row: whole groups of 8 slots
     static constexpr int K_BYTES = 2 * 32 * PITCH;      // hi + lo
-    static constexpr int V_BYTES = 2 * DV * 64;    // hi + lo
+    static constexpr int V_BYTES = 32 * NV * 64;   // hi + lo
     static constexpr int TILE_BYTES = K_BYTES + V_BYTES;
+    static_assert(V_BYTES <= 2 * DV * 64, "selfattn_workspace_bytes has room for parts that are not stacked");
     static constexpr int K_CHUNKS = K_BYTES / 1024, TILE_CHUNKS = TILE_BYTES / 1024;
-    static constexpr int STAGES = 3;
+    // products one tile ahead of the codes (a wide head has no registers for it): one more stage
+    static constexpr int LEAD = KS <= 5 ? 1 : 0;
+    static constexpr int STAGES = 3 + LEAD;
     // direct-to-LDS loads per wave and tile (8 waves): sweep A copies the K part, sweep B all
     static constexpr int LA = K_CHUNKS / 8, LB = (TILE_CHUNKS + 7) / 8;
     // wavefronts per SIMD the registers are budgeted for: the query pieces and the output
@@ -711,8 +735,10 @@ __device__ __host__ inline int v_row_slot(int t, int c) { return t * 64 + ((c ^ 
                  :                                                                    \
                  : "v"(voff), "s"(sbase), "s"(l0)                                     \
                  : "memory", "m0")
+// at most N vector memory operations outstanding, and every LDS read of the wave back: behind the
+// barrier that follows, the stage it read from is written again
 #define DGQ_X_WAIT_VMCNT(N) \
-    __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
+    __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4))
 
 // Write-bound: a tile image is one 16-byte slot of K (eight dims of a key) and one of V^T (eight keys of a
 // dim) per thread and piece, each put together in registers and stored whole, four neighbouring lanes to a
@@ -724,18 +750,18 @@ __global__ __launch_bounds__(256) void k_selfattn_prep(
     const float *__restrict__ k, const float *__restrict__ v, int32_t nk, int32_t H, int32_t d,
     float qk_scale, const float *__restrict__ scale_in, int32_t n_tiles,
     uint8_t *__restrict__ ws) {
-    constexpr int DV = CF::DV;
+    constexpr int VD = CF::VDIMS;
     const int32_t tile = blockIdx.x, head = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x;
     const int64_t hs = (int64_t)H * d;
     const int64_t bh = (int64_t)b * H + head;
     const float s_b = scale_in[b];
-    const float s_eff = s_b > 0.0f ? s_b : 1.0f;
+    const float s_eff = s_b > 0.0f ? s_b : 0.0f;  // scale 0: every product is 0
     const float *kb = k + ((int64_t)b * nk * H + head) * d;
     const float *vb = v + ((int64_t)b * nk * H + head) * d;
     uint8_t *img = ws + (bh * n_tiles + tile) * CF::TILE_BYTES;
     uint8_t *khp = img, *klp = img + 32 * CF::PITCH;
-    uint8_t *vhp = img + CF::K_BYTES, *vlp = vhp + DV * 64;
+    uint8_t *vp = img + CF::K_BYTES;  // high part in rows 0 .., low part in rows VD ..
     constexpr int SLOTS = CF::PITCH / 16;  // eights of dims per K row
     for (int idx = tid; idx < 32 * SLOTS; idx += 256) {
         const int j = idx / SLOTS, c = idx - j * SLOTS, t8 = 8 * c;
@@ -752,7 +778,9 @@ __global__ __launch_bounds__(256) void k_selfattn_prep(
         *reinterpret_cast<u32x4 *>(khp + off) = u32x4{p0.hi, p1.hi, p2.hi, p3.hi};
         *reinterpret_cast<u32x4 *>(klp + off) = u32x4{p0.lo, p1.lo, p2.lo, p3.lo};
     }
-    for (int idx = tid; idx < DV * 4; idx += 256) {
+    for (int idx = tid; idx < CF::V_BYTES / 16 - 2 * VD * 4; idx += 256)  // rows below a stack: no output takes them
+        *reinterpret_cast<u32x4 *>(vp + 2 * VD * 64 + 16 * idx) = u32x4{0u, 0u, 0u, 0u};
+    for (int idx = tid; idx < VD * 4; idx += 256) {
         const int t = idx >> 2, c = idx & 3;
         const int32_t key0 = 32 * tile + 16 * (c >> 1) + 4 * (c & 1);  // element e: key0 + 8 (e / 4) + e % 4 (v_slot)
         float x[8];
@@ -769,9 +797,8 @@ __global__ __launch_bounds__(256) void k_selfattn_prep(
             hb[e] = bf16_rne_bits(xe);
             lb[e] = bf16_rne_bits(xe - __uint_as_float(hb[e]));
         }
-        const int off = v_row_slot(t, c);
-        *reinterpret_cast<u32x4 *>(vhp + off) = u32x4{(hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3], (hb[4] >> 16) | hb[5], (hb[6] >> 16) | hb[7]};
-        *reinterpret_cast<u32x4 *>(vlp + off) = u32x4{(lb[0] >> 16) | lb[1], (lb[2] >> 16) | lb[3], (lb[4] >> 16) | lb[5], (lb[6] >> 16) | lb[7]};
+        *reinterpret_cast<u32x4 *>(vp + v_row_slot(t, c)) = u32x4{(hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3], (hb[4] >> 16) | hb[5], (hb[6] >> 16) | hb[7]};
+        *reinterpret_cast<u32x4 *>(vp + v_row_slot(VD + t, c)) = u32x4{(lb[0] >> 16) | lb[1], (lb[2] >> 16) | lb[3], (lb[4] >> 16) | lb[5], (lb[6] >> 16) | lb[7]};
     }
 }
 
@@ -781,7 +808,7 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     int32_t n_tiles, int32_t q_tiles, const uint8_t *__restrict__ ws,
     const float *__restrict__ scale_in, float *__restrict__ out, float *__restrict__ scale_out,
     uint8_t *__restrict__ codes_dump) {
-    constexpr int KS = CF::KS, DB = CF::DB, DV = CF::DV, STAGES = CF::STAGES;
+    constexpr int KS = CF::KS, DB = CF::DB, STAGES = CF::STAGES, LEAD = CF::LEAD, NV = CF::NV, NO = CF::NO;
     extern __shared__ __attribute__((aligned(1024))) uint8_t ring[];
     // Workgroup w runs on XCD w % 8: give every XCD whole (prompt, head) pairs, so that the
     // pair's tile images (2 MB at 4096 keys) are fetched into one L2 only.
@@ -800,24 +827,31 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
 
     const float s_b = scale_in[b];
     const float s_eff = s_b > 0.0f ? s_b : 1.0f;
-    const uint32_t pmask = s_b > 0.0f ? 0xFFFFFFFFu : 0u;  // scale 0: every product is 0
     const float l2s = __log2f(s_eff);
 
-    // ---- the lane's query slices as fp16 pieces: dims 16 s + 8 hh .. + 7 -------------------
+    // ---- the lane's query slices as fp16 pieces: dims 16 s + 8 hh .. + 7; of half a step both lane
+    // halves take the same eight, as [Qh Ql] and [Qh 0] --------------------------------------------
     u32x4 qh[KS], ql[KS];
     {
-        const float *p = q + ((int64_t)b * N * H + head) * d + (int64_t)(valid ? qi : N - 1) * hs + 8 * hh;
+        const float *p = q + ((int64_t)b * N * H + head) * d + (int64_t)(valid ? qi : N - 1) * hs ;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
+            const bool half = CF::HALF && s == KS - 1;
+            const int at = 16 * s + (half ? 0 : 8 * hh);
             float4 a = {0.0f, 0.0f, 0.0f, 0.0f}, c = a;
-            if (16 * s + 8 * hh < d) {
-                a = *reinterpret_cast<const float4 *>(p + 16 * s);
-                c = *reinterpret_cast<const float4 *>(p + 16 * s + 4);
+            if (at < d) {
+                a = *reinterpret_cast<const float4 *>(p + at);
+                c = *reinterpret_cast<const float4 *>(p + at + 4);
             }
             const HiLo p0 = split_h2(a.x, a.y), p1 = split_h2(a.z, a.w);
             const HiLo p2 = split_h2(c.x, c.y), p3 = split_h2(c.z, c.w);
             qh[s] = u32x4{p0.hi, p1.hi, p2.hi, p3.hi};
             ql[s] = u32x4{p0.lo, p1.lo, p2.lo, p3.lo};
+            if (half) {
+                const u32x4 hi = qh[s], lo = ql[s];
+                qh[s] = hh ? lo : hi;
+                ql[s] = hh ? u32x4{0u, 0u, 0u, 0u} : hi;
+            }
         }
     }
 
@@ -839,12 +873,12 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
             DGQ_X_LDS_DMA16(src + c * 1024, lane16, dst + (uint32_t)c * 1024u);
         }
     };
-    // One step of a sweep: tile kt has landed for every wave, and the stage the tile after
-    // next goes to is no longer read by anyone.
+    // One step of a sweep: tile kt + LEAD has landed for every wave, and the stage of tile kt - 1 is no
+    // longer read by anyone: the next tile to load, kt - 1 + STAGES, goes there.  One tile stays in flight.
     auto advance = [&](const bool with_v, int32_t kt) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
         // the code dump's stores share the counter and need not return in order with loads
-        if (DUMP || kt + 1 >= n_tiles)
+        if (DUMP || kt + LEAD + 1 >= n_tiles)
             DGQ_X_WAIT_VMCNT(0);
         else if (with_v)
             DGQ_X_WAIT_VMCNT(CF::LB);
@@ -852,31 +886,27 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
             DGQ_X_WAIT_VMCNT(CF::LA);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (kt + 2 < n_tiles) issue(with_v, kt + 2);
+        if (kt + STAGES - 1 < n_tiles) issue(with_v, kt + STAGES - 1);
     };
 
     const int k_row = n * CF::PITCH, k_key = k_row_key(CF::PITCH, n) ^ hh;  // slot 2 s + hh of row n
-    // S^T of the tile in `stage` for the wave's 32 queries, in log2 units; padding keys -inf
-    auto s_tile = [&](int32_t kt, v16f &sm) {
+    // S^T + start of tile kt for the wave's 32 queries, in log2 units
+    auto s_tile = [&](int32_t kt, float start, v16f &sm) __attribute__((always_inline)) {
         const uint8_t *st = ring + (kt % STAGES) * CF::TILE_BYTES;
         // all fragments of a narrow head are read up front; a wide head (whose query pieces
         // and output blocks fill the register file) reads them one step ahead of their MFMAs
         constexpr int NF = KS <= 4 ? KS : 2;
         u32x4 fh[NF], fl[NF];
         auto frag = [&](int s) __attribute__((always_inline)) {
-            const int off = k_row + ((k_key ^ (2 * s)) << 4);
+            const int key = CF::HALF && s == KS - 1 ? k_key ^ hh : k_key;
+            const int off = k_row + ((key ^ (2 * s)) << 4);
             fh[s % NF] = *reinterpret_cast<const u32x4 *>(st + off);
             fl[s % NF] = *reinterpret_cast<const u32x4 *>(st + 32 * CF::PITCH + off);
         };
 #pragma unroll
         for (int s = 0; s < (KS <= 4 ? KS : 1); ++s) frag(s);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sm[i] = 0.0f;
-        if (32 * kt + 32 > nk) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (32 * kt + key_of(0, i, hh) >= nk) sm[i] = -INFINITY;
-        }
+        for (int i = 0; i < 16; ++i) sm[i] = start;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             if (KS > 4 && s + 1 < KS) frag(s + 1);
@@ -885,37 +915,113 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
             const v8h akh = __builtin_bit_cast(v8h, fh[s % NF]);
             const v8h akl = __builtin_bit_cast(v8h, fl[s % NF]);
             sm = __builtin_amdgcn_mfma_f32_32x32x16_f16(akh, bqh, sm, 0, 0, 0);
-            sm = __builtin_amdgcn_mfma_f32_32x32x16_f16(akh, bql, sm, 0, 0, 0);
-            sm = __builtin_amdgcn_mfma_f32_32x32x16_f16(akl, bqh, sm, 0, 0, 0);
+            if (CF::HALF && s == KS - 1) {
+                sm = __builtin_amdgcn_mfma_f32_32x32x16_f16(akl, bql, sm, 0, 0, 0);
+            } else {
+                sm = __builtin_amdgcn_mfma_f32_32x32x16_f16(akh, bql, sm, 0, 0, 0);
+                sm = __builtin_amdgcn_mfma_f32_32x32x16_f16(akl, bqh, sm, 0, 0, 0);
+            }
         }
+    };
+    // padding keys of the last tile: -inf
+    auto mask_tail = [&](v16f &sm) __attribute__((always_inline)) {
+        if (32 * n_tiles > nk) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (32 * (n_tiles - 1) + key_of(0, i, hh) >= nk) sm[i] = -INFINITY;
+        }
+    };
+    auto start_ring = [&](const bool with_v) __attribute__((always_inline)) {
+        issue(with_v, 0);
+        if (n_tiles > 1) issue(with_v, 1);
+        if (LEAD) advance(with_v, -1);
     };
 
     // ---- sweep A: lse2 of the lane's query (each lane half sees half of the keys) -------
-    float m = -INFINITY, l = 0.0f;
-    issue(false, 0);
-    if (n_tiles > 1) issue(false, 1);
-    for (int32_t kt = 0; kt < n_tiles; ++kt) {
-        advance(false, kt);
-        v16f sm;
-        s_tile(kt, sm);
-        float tm = sm[0];
+    // The sum is kept relative to `ref`, the lane's maximum over its first tile, which enters as the start
+    // value of the products: no subtraction per logit, and a later, larger logit only makes terms above 1.
+    // A tile whose sum passes 2^64 moves `ref` up (a branch hardly ever taken: a logit 59 octaves and more
+    // above the first tile's largest), so the running sum stays below 2^64 times the number of tiles.  It
+    // carries its rounding error along.  The maximum itself is followed only where it is reported.
+    float ref = 0.0f, l = 0.0f, lc = 0.0f, mx = -INFINITY;  // mx relative to ref, the sum is l + lc
+    auto sum16 = [&](const v16f &x) __attribute__((always_inline)) {
+        float e[4];
 #pragma unroll
-        for (int i = 1; i < 16; ++i) tm = fmaxf(tm, sm[i]);
-        const float mn = fmaxf(m, tm);
-        const float ms = mn == -INFINITY ? 0.0f : mn;
-        float add = 0.0f;
+        for (int i = 0; i < 4; ++i) e[i] = __builtin_amdgcn_exp2f(x[i]);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) add += __builtin_amdgcn_exp2f(sm[i] - ms);
-        l = l * __builtin_amdgcn_exp2f(m - ms) + add;
-        m = mn;
+        for (int i = 4; i < 16; ++i) e[i & 3] += __builtin_amdgcn_exp2f(x[i]);
+        return (e[0] + e[1]) + (e[2] + e[3]);
+    };
+    // a tile's logits sm into the sum; `next`: the logits of the tile after it, relative to the same ref
+    auto add_tile = [&](const bool first, v16f &sm, v16f &next) __attribute__((always_inline)) {
+        float add = sum16(sm);
+        const bool move = first || !(add < 0x1p64f);
+        if (__any(move)) {
+            float tm = sm[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) tm = fmaxf(tm, sm[i]);
+            // lanes that stay, and a lane half with padding keys only (-inf), move by 0
+            const float up = move && tm > -INFINITY ? tm : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                sm[i] -= up;
+                next[i] -= up;
+            }
+            add = sum16(sm);
+            const float f = __builtin_amdgcn_exp2f(fminf(-up, 0.0f));  // the first tile alone moves down: l = 0
+            l *= f;
+            lc *= f;
+            mx -= up;
+            ref += up;
+        }
+        const float t = l + add, back = t - l;
+        lc += (l - (t - back)) + (add - back);  // what the addition lost, exactly
+        l = t;
+        if (scale_out) {
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(mx, sm[i]), sm[i + 1]);
+        }
+    };
+    start_ring(false);
+    if (LEAD) {
+        v16f sm, next;
+        s_tile(0, 0.0f, sm);
+        if (n_tiles > 1) {
+            advance(false, 0);
+            s_tile(1, 0.0f, next);
+            add_tile(true, sm, next);
+            sm = next;
+            for (int32_t kt = 1; kt + 1 < n_tiles; ++kt) {
+                advance(false, kt);
+                s_tile(kt + 1, -ref, next);
+                add_tile(false, sm, next);
+                sm = next;
+            }
+        }
+        mask_tail(sm);
+        next = sm;
+        add_tile(n_tiles == 1, sm, next);
+    } else {
+        for (int32_t kt = 0; kt < n_tiles; ++kt) {
+            advance(false, kt);
+            v16f sm;
+            s_tile(kt, -ref, sm);
+            if (kt + 1 == n_tiles) mask_tail(sm);
+            v16f none = sm;
+            add_tile(kt == 0, sm, none);
+        }
     }
+    l += lc;
     float lse;
     {
-        const float mo = __shfl_xor(m, 32, kWave), lo = __shfl_xor(l, 32, kWave);
-        const float m2 = fmaxf(m, mo);  // finite: key 0 exists
-        const float l2 = l * __builtin_amdgcn_exp2f(m - m2) + lo * __builtin_amdgcn_exp2f(mo - m2);
-        lse = m2 + __log2f(l2);
+        // a lane half that saw no key has no reference either
+        const float r = l == 0.0f ? -INFINITY : ref;
+        const float ro = __shfl_xor(r, 32, kWave), lo = __shfl_xor(l, 32, kWave);
+        const float r2 = fmaxf(r, ro);  // finite: key 0 exists
+        const float l2 = l * __builtin_amdgcn_exp2f(r - r2) + lo * __builtin_amdgcn_exp2f(ro - r2);
+        lse = r2 + __log2f(l2);
         if (scale_out) {
+            const float m = mx + ref, m2 = fmaxf(m, __shfl_xor(m, 32, kWave));
             // the row's largest probability; probabilities order like their bit patterns
             float amax = valid ? m2 - lse : -INFINITY;
             amax = wave_max(amax);
@@ -926,6 +1032,7 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     }
 
     // ---- sweep B: codes and Out^T = V^T P^T -------------------------------------------------
+    // (the products start from 0 here: started from -c0, every accumulation would round at c0's magnitude)
     const float c0 = l2s + lse;
     const float thr = l2s + 150.0f;
     constexpr int32_t kMagic = 0x4B400000;  // bit pattern of 12582912.0f
@@ -935,35 +1042,27 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     const int32_t ce = cq < 127 ? cq : 127;  // 2^-127 and below leave the product as zero
     uint8_t *cd = nullptr;
     if (DUMP) cd = codes_dump + ((int64_t)bh * N + (valid ? qi : 0)) * (int64_t)nk;
-    v16f o[DB];
+    v16f o[NO];
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int ob = 0; ob < NO; ++ob)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o[db][i] = 0.0f;
+        for (int i = 0; i < 16; ++i) o[ob][i] = 0.0f;
     const int v_off = v_row_slot(n, hh);  // slot 2 u + hh: the step enters as an XOR of 2 u
-    __builtin_amdgcn_s_barrier();  // every wave has left sweep A's last stage
-    asm volatile("" ::: "memory");
-    issue(true, 0);
-    if (n_tiles > 1) issue(true, 1);
-    for (int32_t kt = 0; kt < n_tiles; ++kt) {
-        advance(true, kt);
-        v16f sm;
-        s_tile(kt, sm);
+    // codes of tile kt from its logits, and its share of the product
+    auto code_tile = [&](int32_t kt, const v16f &sm) __attribute__((always_inline)) {
         const uint8_t *st = ring + (kt % STAGES) * CF::TILE_BYTES + CF::K_BYTES;
         // V^T fragments of this tile.  Narrow heads: all read before the code arithmetic that
         // hides them; wide heads: each right before its MFMAs (registers)
-        constexpr bool V_AHEAD = DB <= 2;
-        auto v_frag = [&](int db, int u, u32x4 &h, u32x4 &l) __attribute__((always_inline)) {
-            const int off = db * 32 * 64 + (v_off ^ (u << 5));
-            h = *reinterpret_cast<const u32x4 *>(st + off);
-            l = *reinterpret_cast<const u32x4 *>(st + DV * 64 + off);
+        constexpr bool V_AHEAD = KS <= 4;
+        auto v_frag = [&](int vb, int u) __attribute__((always_inline)) {
+            return *reinterpret_cast<const u32x4 *>(st + vb * 32 * 64 + (v_off ^ (u << 5)));
         };
-        u32x4 fvh[V_AHEAD ? DB : 1][2], fvl[V_AHEAD ? DB : 1][2];
+        u32x4 fv[V_AHEAD ? NV : 1][2];
         if (V_AHEAD) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+            for (int vb = 0; vb < NV; ++vb)
 #pragma unroll
-                for (int u = 0; u < 2; ++u) v_frag(db, u, fvh[V_AHEAD ? db : 0][u], fvl[V_AHEAD ? db : 0][u]);
+                for (int u = 0; u < 2; ++u) fv[V_AHEAD ? vb : 0][u] = v_frag(vb, u);
         }
         uint32_t pk[8];
 #pragma unroll
@@ -983,38 +1082,60 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
                 }
                 m[u] = (uint32_t)clamp_i32(r, kMagic - ce, kMagic);
             }
-            pk[i >> 1] = ((m[0] << 7) + ((m[1] << 23) + kPairBase)) & pmask;
+            pk[i >> 1] = (m[0] << 7) + ((m[1] << 23) + kPairBase);
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const u32x4 pb = {pk[4 * u + 0], pk[4 * u + 1], pk[4 * u + 2], pk[4 * u + 3]};
             const v8bf bp = __builtin_bit_cast(v8bf, pb);
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                u32x4 h, l;
-                if (V_AHEAD) {
-                    h = fvh[V_AHEAD ? db : 0][u];
-                    l = fvl[V_AHEAD ? db : 0][u];
-                } else {
-                    v_frag(db, u, h, l);
-                }
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, h), bp, o[db], 0, 0, 0);
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, l), bp, o[db], 0, 0, 0);
+            for (int i = 0; i < NV; ++i) {
+                const int vb = CF::STACK ? i : (i >> 1) + DB * (i & 1), ob = CF::STACK ? vb : i >> 1;
+                const u32x4 f = V_AHEAD ? fv[V_AHEAD ? vb : 0][u] : v_frag(vb, u);
+                o[ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, f), bp, o[ob], 0, 0, 0);
             }
+        }
+    };
+    __builtin_amdgcn_s_barrier();  // every wave has left sweep A's last stage
+    asm volatile("" ::: "memory");
+    start_ring(true);
+    if (LEAD) {
+        v16f sm, next;
+        s_tile(0, 0.0f, sm);
+        for (int32_t kt = 0; kt + 1 < n_tiles; ++kt) {
+            advance(true, kt);
+            s_tile(kt + 1, 0.0f, next);
+            code_tile(kt, sm);
+            sm = next;
+        }
+        mask_tail(sm);
+        code_tile(n_tiles - 1, sm);
+    } else {
+        for (int32_t kt = 0; kt < n_tiles; ++kt) {
+            advance(true, kt);
+            v16f sm;
+            s_tile(kt, 0.0f, sm);
+            if (kt + 1 == n_tiles) mask_tail(sm);
+            code_tile(kt, sm);
         }
     }
     if (valid) {
         float *orow = out + ((int64_t)b * N * H + head) * d + (int64_t)qi * hs;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const int dim = 32 * db + 8 * a + 4 * hh;
-                if (dim < d) {
-                    const float4 t = {o[db][4 * a + 0], o[db][4 * a + 1], o[db][4 * a + 2], o[db][4 * a + 3]};
-                    *reinterpret_cast<float4 *>(orow + dim) = t;
+        for (int g = 0; g < (CF::STACK ? CF::D8 : 4 * DB); ++g) {  // eights of output dims, four per lane half
+            const int dim = 8 * g + 4 * hh;
+            if (dim < d) {
+                float4 t = {o[g / 4][4 * (g % 4) + 0], o[g / 4][4 * (g % 4) + 1], o[g / 4][4 * (g % 4) + 2], o[g / 4][4 * (g % 4) + 3]};
+                if (CF::STACK) {
+                    const int l0 = (g + CF::D8) / 4, a = 4 * ((g + CF::D8) % 4);
+                    t.x += o[l0 % NO][a + 0];
+                    t.y += o[l0 % NO][a + 1];
+                    t.z += o[l0 % NO][a + 2];
+                    t.w += o[l0 % NO][a + 3];
                 }
+                *reinterpret_cast<float4 *>(orow + dim) = t;
             }
+        }
     }
 }
 
@@ -1463,20 +1584,28 @@ size_t selfattn_workspace_bytes(int32_t B, int32_t N, int32_t H, int32_t d) {
     if (d % 8 != 0 || d > 160 || d < 8) return 0;
     const size_t ks = (size_t)selfattn_ks(d), dv = 32 * ((ks + 1) / 2), pitch = 128 * ((ks + 3) / 4);
     const size_t n_tiles = ((size_t)N + 31) / 32;
-    return (size_t)B * H * n_tiles * (2 * 32 * pitch + 2 * dv * 64);  // one tile image per 32 keys
+    return (size_t)B * H * n_tiles * (2 * 32 * pitch + 2 * dv * 64);  // one tile image per 32 keys, at most
 }
 
 hipError_t launch_selfattn(const float *q, const float *k, const float *v, int32_t B, int32_t N,
                            int32_t H, int32_t d, int32_t bits, const float *scale_in, float *out,
                            float *scale_out, uint8_t *codes_dump, void *workspace, hipStream_t st) {
-    switch (selfattn_ks(d)) {
-        case 1: return launch_selfattn_cfg<SCfg<1>>(q, k, v, B, N, H, d, bits, scale_in, out, scale_out, codes_dump, workspace, st);
-        case 2: return launch_selfattn_cfg<SCfg<2>>(q, k, v, B, N, H, d, bits, scale_in, out, scale_out, codes_dump, workspace, st);
-        case 3: return launch_selfattn_cfg<SCfg<3>>(q, k, v, B, N, H, d, bits, scale_in, out, scale_out, codes_dump, workspace, st);
-        case 4: return launch_selfattn_cfg<SCfg<4>>(q, k, v, B, N, H, d, bits, scale_in, out, scale_out, codes_dump, workspace, st);
-        case 5: return launch_selfattn_cfg<SCfg<5>>(q, k, v, B, N, H, d, bits, scale_in, out, scale_out, codes_dump, workspace, st);
-        default: return launch_selfattn_cfg<SCfg<10>>(q, k, v, B, N, H, d, bits, scale_in, out, scale_out, codes_dump, workspace, st);
+#define DGQ_SELFATTN(...) \
+    launch_selfattn_cfg<SCfg<__VA_ARGS__>>(q, k, v, B, N, H, d, bits, scale_in, out, scale_out, codes_dump, workspace, st)
+    switch (d) {  // up to 80 dims a kernel each
+        case 8: return DGQ_SELFATTN(1, true);
+        case 16: return DGQ_SELFATTN(1);
+        case 24: return DGQ_SELFATTN(2, true);
+        case 32: return DGQ_SELFATTN(2);
+        case 40: return DGQ_SELFATTN(3, true);
+        case 48: return DGQ_SELFATTN(3);
+        case 56: return DGQ_SELFATTN(4, true);
+        case 64: return DGQ_SELFATTN(4);
+        case 72: return DGQ_SELFATTN(5, true);
+        case 80: return DGQ_SELFATTN(5);
+        default: return DGQ_SELFATTN(10);
     }
+#undef DGQ_SELFATTN
 }
 
 }  // namespace dgq

@@ -80,6 +80,46 @@ def test_small_shapes(dgq, oracle, B, N, H, d, bits):
         assert np.unique(ref["codes"]).size > 10          # the codes span many octaves
 
 
+@pytest.mark.parametrize("B,N,H,d", [
+    (1, 65, 2, 24),     # half a 16-dim step; high and low part of V^T in blocks of their own
+    (2, 97, 1, 48),     # whole steps, V^T stacked
+    (1, 129, 1, 56),    # half a step, no stack
+    (1, 31, 2, 40),     # both, and a single ragged tile
+    (1, 64, 1, 72),     # both, with fragments read a step ahead; two whole tiles
+    (9, 32, 1, 64),     # one whole tile, more pairs than XCDs
+])
+def test_packed_head_widths(dgq, oracle, B, N, H, d):
+    c = di.selfattn_case(400 + N + d, B, N, H, d)
+    _check(dgq, oracle, c, 8, np.linspace(1.0, 0.25, B, dtype=np.float32), min_good=0.5)
+
+
+@pytest.mark.parametrize("d", [40, 64, 160])
+@pytest.mark.parametrize("levels", [
+    {0: 250.0},                          # the first tile holds the maximum, nothing after it counts
+    {40: 130.0, 100: 250.0},             # the sum's reference is left behind twice, far above 2^64
+    {33: 50.0, 70: 100.0, 129: 200.0},   # in steps around that limit, the last in a ragged tile
+    {0: -300.0, 5: 200.0, 99: 200.0},    # two equal maxima: half the weight each
+])
+def test_logits_that_outgrow_the_first_tile(dgq, levels, d):
+    """Keys whose logits (natural units) stand so far apart that only the largest have any weight: the product is
+    their mean, to the 2^-17 of V's two bf16 pieces, and the largest probability 1 or 1/2."""
+    import torch
+    N = 131
+    g = torch.Generator().manual_seed(d)
+    q, k = torch.zeros(1, N, 1, d), torch.zeros(1, N, 1, d)
+    v = torch.randn(1, N, 1, d, generator=g)
+    q[..., 0] = 1.0
+    for j, level in levels.items():
+        k[0, j, 0, 0] = level * d ** 0.5
+    top = [j for j in levels if levels[j] == max(levels.values())]
+    s_out = torch.zeros(1, device="cuda")
+    out = dgq.dgq_selfattn_logq(q.cuda(), k.cuda(), v.cuda(), 8, torch.ones(1, device="cuda"), scale_out=s_out)
+    torch.cuda.synchronize()
+    want = v[0, top].double().mean(0)
+    assert (out.cpu().double()[0] - want).abs().max() <= 2.0 ** -16 * want.abs().max()
+    assert abs(float(s_out) * len(top) - 1.0) <= 1e-5
+
+
 def test_scale_at_the_maximum_and_below(dgq, oracle):
     """Given the call's own maximum the largest probability takes code 0; a smaller scale
     saturates everything above it; a scale of zero gives a zero product."""
