@@ -660,8 +660,8 @@ bool mfma_shape(int32_t d, int32_t nk) {
 // reads of 32 consecutive rows spread over all banks.  The second kernel gives each of its
 // eight wavefronts 32 queries (their fp16 pieces stay in registers) and sweeps the key tiles
 // twice through a four-stage LDS ring (three for the widest heads) filled by direct-to-LDS loads of 1 KiB (the tile
-// image is copied verbatim): sweep A takes the sum of 2^(S - ref), ref the maximum of the
-// first tile, for lse2, sweep B recomputes S^T bit-identically, forms the codes from log2 s + lse2 - S as
+// image is copied verbatim): sweep A takes the running maximum and sum of 2^(S - max) for
+// lse2, sweep B recomputes S^T bit-identically, forms the codes from log2 s + lse2 - S as
 // above and accumulates Out^T = V^T P^T.  A code depends on the row's full sum, so one
 // sweep cannot do both.  (Read straight from memory by every wavefront, the fragments cost
 // 24 KB of cache traffic per wavefront and tile pair and the texture path, not the matrix
@@ -676,9 +676,11 @@ bool mfma_shape(int32_t d, int32_t nk) {
 // And the products of tile kt + 1 are issued among the exponentials or codes of tile kt, from which they are
 // independent: at 2 x 8 x 4096 x 40 the launch is one workgroup per CU, two wavefronts per SIMD, which a
 // barrier per tile keeps in phase, so that nobody else's vector work would fill the matrix instructions' time.
-// Measured, the call before and now, us: 2 x 8 x 4096 x 40 211 -> 193; in another run (B x N x H x d)
-// 8 x 1024 x 10 x 40 99.9 -> 91.3, 2 x 2100 x 8 x 48 105 -> 98, 2 x 1024 x 8 x 80 77.7 -> 74.4,
-// 16 x 4096 x 10 x 64 2310 -> 2271.
+// Measured, the call before and now, us: 2 x 8 x 4096 x 40 211 -> 189; in another run (B x N x H x d)
+// 8 x 1024 x 10 x 40 99.9 -> 88.4, 2 x 2000 x 8 x 24 83.6 -> 70.6, 2 x 2100 x 8 x 48 105 -> 94,
+// 2 x 1024 x 8 x 80 77.7 -> 71.5, 16 x 4096 x 10 x 64 2310 -> 2234.  The codes have the same bits as without
+// the packing.  Kept relative to the first tile's maximum as the products' start value, the row sum saved a
+// subtraction per logit and the maxima (183 us), but moved one code in 10^6 across its rounding boundary.
 template <int KS_, bool HALF_ = false>
 struct SCfg {
     static constexpr int KS = KS_;
@@ -890,8 +892,8 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     };
 
     const int k_row = n * CF::PITCH, k_key = k_row_key(CF::PITCH, n) ^ hh;  // slot 2 s + hh of row n
-    // S^T + start of tile kt for the wave's 32 queries, in log2 units
-    auto s_tile = [&](int32_t kt, float start, v16f &sm) __attribute__((always_inline)) {
+    // S^T of tile kt for the wave's 32 queries, in log2 units
+    auto s_tile = [&](int32_t kt, v16f &sm) __attribute__((always_inline)) {
         const uint8_t *st = ring + (kt % STAGES) * CF::TILE_BYTES;
         // all fragments of a narrow head are read up front; a wide head (whose query pieces
         // and output blocks fill the register file) reads them one step ahead of their MFMAs
@@ -906,7 +908,7 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
 #pragma unroll
         for (int s = 0; s < (KS <= 4 ? KS : 1); ++s) frag(s);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sm[i] = start;
+        for (int i = 0; i < 16; ++i) sm[i] = 0.0f;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             if (KS > 4 && s + 1 < KS) frag(s + 1);
@@ -938,90 +940,58 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     };
 
     // ---- sweep A: lse2 of the lane's query (each lane half sees half of the keys) -------
-    // The sum is kept relative to `ref`, the lane's maximum over its first tile, which enters as the start
-    // value of the products: no subtraction per logit, and a later, larger logit only makes terms above 1.
-    // A tile whose sum passes 2^64 moves `ref` up (a branch hardly ever taken: a logit 59 octaves and more
-    // above the first tile's largest), so the running sum stays below 2^64 times the number of tiles.  It
-    // carries its rounding error along.  The maximum itself is followed only where it is reported.
-    float ref = 0.0f, l = 0.0f, lc = 0.0f, mx = -INFINITY;  // mx relative to ref, the sum is l + lc
-    auto sum16 = [&](const v16f &x) __attribute__((always_inline)) {
-        float e[4];
+    // (the products start from 0 in both sweeps: started from minus a row's maximum or lse2, every accumulation
+    // would round at that magnitude)
+    float m = -INFINITY, l = 0.0f;
+    auto add_tile = [&](const v16f &sm) __attribute__((always_inline)) {
+        float tm = sm[0];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) e[i] = __builtin_amdgcn_exp2f(x[i]);
+        for (int i = 1; i < 16; ++i) tm = fmaxf(tm, sm[i]);
+        const float mn = fmaxf(m, tm);
+        const float ms = mn == -INFINITY ? 0.0f : mn;
+        float add = 0.0f;
 #pragma unroll
-        for (int i = 4; i < 16; ++i) e[i & 3] += __builtin_amdgcn_exp2f(x[i]);
-        return (e[0] + e[1]) + (e[2] + e[3]);
-    };
-    // a tile's logits sm into the sum; `next`: the logits of the tile after it, relative to the same ref
-    auto add_tile = [&](const bool first, v16f &sm, v16f &next) __attribute__((always_inline)) {
-        float add = sum16(sm);
-        const bool move = first || !(add < 0x1p64f);
-        if (__any(move)) {
-            float tm = sm[0];
-#pragma unroll
-            for (int i = 1; i < 16; ++i) tm = fmaxf(tm, sm[i]);
-            // lanes that stay, and a lane half with padding keys only (-inf), move by 0
-            const float up = move && tm > -INFINITY ? tm : 0.0f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                sm[i] -= up;
-                next[i] -= up;
-            }
-            add = sum16(sm);
-            const float f = __builtin_amdgcn_exp2f(fminf(-up, 0.0f));  // the first tile alone moves down: l = 0
-            l *= f;
-            lc *= f;
-            mx -= up;
-            ref += up;
-        }
-        const float t = l + add, back = t - l;
-        lc += (l - (t - back)) + (add - back);  // what the addition lost, exactly
-        l = t;
-        if (scale_out) {
-#pragma unroll
-            for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(mx, sm[i]), sm[i + 1]);
-        }
+        for (int i = 0; i < 16; ++i) add += __builtin_amdgcn_exp2f(sm[i] - ms);
+        l = l * __builtin_amdgcn_exp2f(m - ms) + add;
+        m = mn;
     };
     start_ring(false);
     if (LEAD) {
         v16f sm, next;
-        s_tile(0, 0.0f, sm);
-        if (n_tiles > 1) {
-            advance(false, 0);
-            s_tile(1, 0.0f, next);
-            add_tile(true, sm, next);
+        s_tile(0, sm);
+        int32_t kt = 0;
+        for (; kt + 2 < n_tiles; kt += 2) {  // by two: the two sets of logits change places without copies
+            advance(false, kt);
+            s_tile(kt + 1, next);
+            add_tile(sm);
+            advance(false, kt + 1);
+            s_tile(kt + 2, sm);
+            add_tile(next);
+        }
+        if (kt + 1 < n_tiles) {
+            advance(false, kt);
+            s_tile(kt + 1, next);
+            add_tile(sm);
             sm = next;
-            for (int32_t kt = 1; kt + 1 < n_tiles; ++kt) {
-                advance(false, kt);
-                s_tile(kt + 1, -ref, next);
-                add_tile(false, sm, next);
-                sm = next;
-            }
         }
         mask_tail(sm);
-        next = sm;
-        add_tile(n_tiles == 1, sm, next);
+        add_tile(sm);
     } else {
         for (int32_t kt = 0; kt < n_tiles; ++kt) {
             advance(false, kt);
             v16f sm;
-            s_tile(kt, -ref, sm);
+            s_tile(kt, sm);
             if (kt + 1 == n_tiles) mask_tail(sm);
-            v16f none = sm;
-            add_tile(kt == 0, sm, none);
+            add_tile(sm);
         }
     }
-    l += lc;
     float lse;
     {
-        // a lane half that saw no key has no reference either
-        const float r = l == 0.0f ? -INFINITY : ref;
-        const float ro = __shfl_xor(r, 32, kWave), lo = __shfl_xor(l, 32, kWave);
-        const float r2 = fmaxf(r, ro);  // finite: key 0 exists
-        const float l2 = l * __builtin_amdgcn_exp2f(r - r2) + lo * __builtin_amdgcn_exp2f(ro - r2);
-        lse = r2 + __log2f(l2);
+        const float mo = __shfl_xor(m, 32, kWave), lo = __shfl_xor(l, 32, kWave);
+        const float m2 = fmaxf(m, mo);  // finite: key 0 exists
+        const float l2 = l * __builtin_amdgcn_exp2f(m - m2) + lo * __builtin_amdgcn_exp2f(mo - m2);
+        lse = m2 + __log2f(l2);
         if (scale_out) {
-            const float m = mx + ref, m2 = fmaxf(m, __shfl_xor(m, 32, kWave));
             // the row's largest probability; probabilities order like their bit patterns
             float amax = valid ? m2 - lse : -INFINITY;
             amax = wave_max(amax);
@@ -1032,7 +1002,6 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     }
 
     // ---- sweep B: codes and Out^T = V^T P^T -------------------------------------------------
-    // (the products start from 0 here: started from -c0, every accumulation would round at c0's magnitude)
     const float c0 = l2s + lse;
     const float thr = l2s + 150.0f;
     constexpr int32_t kMagic = 0x4B400000;  // bit pattern of 12582912.0f
@@ -1082,7 +1051,9 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
                 }
                 m[u] = (uint32_t)clamp_i32(r, kMagic - ce, kMagic);
             }
-            pk[i >> 1] = (m[0] << 7) + ((m[1] << 23) + kPairBase);
+            uint32_t hi = (m[1] << 23) + kPairBase;
+            asm("" : "+v"(hi));  // two shift-and-adds; reassociated they are two shifts and an addition of three
+            pk[i >> 1] = (m[0] << 7) + hi;
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -1101,10 +1072,19 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     start_ring(true);
     if (LEAD) {
         v16f sm, next;
-        s_tile(0, 0.0f, sm);
-        for (int32_t kt = 0; kt + 1 < n_tiles; ++kt) {
+        s_tile(0, sm);
+        int32_t kt = 0;
+        for (; kt + 2 < n_tiles; kt += 2) {
             advance(true, kt);
-            s_tile(kt + 1, 0.0f, next);
+            s_tile(kt + 1, next);
+            code_tile(kt, sm);
+            advance(true, kt + 1);
+            s_tile(kt + 2, sm);
+            code_tile(kt + 1, next);
+        }
+        if (kt + 1 < n_tiles) {
+            advance(true, kt);
+            s_tile(kt + 1, next);
             code_tile(kt, sm);
             sm = next;
         }
@@ -1114,7 +1094,7 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
         for (int32_t kt = 0; kt < n_tiles; ++kt) {
             advance(true, kt);
             v16f sm;
-            s_tile(kt, 0.0f, sm);
+            s_tile(kt, sm);
             if (kt + 1 == n_tiles) mask_tail(sm);
             code_tile(kt, sm);
         }

@@ -96,8 +96,8 @@ def test_packed_head_widths(dgq, oracle, B, N, H, d):
 @pytest.mark.parametrize("d", [40, 64, 160])
 @pytest.mark.parametrize("levels", [
     {0: 250.0},                          # the first tile holds the maximum, nothing after it counts
-    {40: 130.0, 100: 250.0},             # the sum's reference is left behind twice, far above 2^64
-    {33: 50.0, 70: 100.0, 129: 200.0},   # in steps around that limit, the last in a ragged tile
+    {40: 130.0, 100: 250.0},             # the running maximum moves twice, by more than the sum's range
+    {33: 50.0, 70: 100.0, 129: 200.0},   # in smaller steps, the last in a ragged tile
     {0: -300.0, 5: 200.0, 99: 200.0},    # two equal maxima: half the weight each
 ])
 def test_logits_that_outgrow_the_first_tile(dgq, levels, d):
