@@ -741,6 +741,7 @@ __device__ __host__ inline int v_row_slot(int t, int c) { return t * 64 + ((c ^ 
 // barrier that follows, the stage it read from is written again
 #define DGQ_X_WAIT_VMCNT(N) \
     __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4))
+#define DGQ_X_WAIT_LDS() DGQ_X_WAIT_VMCNT(63)  // the LDS reads alone: 63, the counter's end, stands for no wait
 
 // Write-bound: a tile image is one 16-byte slot of K (eight dims of a key) and one of V^T (eight keys of a
 // dim) per thread and piece, each put together in registers and stored whole, four neighbouring lanes to a
@@ -1067,7 +1068,10 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
             }
         }
     };
-    __builtin_amdgcn_s_barrier();  // every wave has left sweep A's last stage
+    // every wave has left sweep A's last stage, its reads included: the copies behind the barrier may go there
+    asm volatile("" ::: "memory");
+    DGQ_X_WAIT_LDS();
+    __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     start_ring(true);
     if (LEAD) {

@@ -93,6 +93,16 @@ def test_packed_head_widths(dgq, oracle, B, N, H, d):
     _check(dgq, oracle, c, 8, np.linspace(1.0, 0.25, B, dtype=np.float32), min_good=0.5)
 
 
+@pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 6])
+@pytest.mark.parametrize("d", [40, 128])
+def test_tile_counts_of_the_ring(dgq, oracle, d, tiles):
+    """Sweep B's first copies go to stages 0 and 1, whichever stage sweep A's last tile was read from: every residue of
+    the tile count by the four stages (d <= 80) and the three (above), the last tile whole or ragged."""
+    N = 32 * tiles - (tiles & 1)
+    c = di.selfattn_case(600 + tiles + d, 2, N, 2, d)
+    _check(dgq, oracle, c, 8, np.array([1.0, 0.25], np.float32), min_good=0.5)
+
+
 @pytest.mark.parametrize("d", [40, 64, 160])
 @pytest.mark.parametrize("levels", [
     {0: 250.0},                          # the first tile holds the maximum, nothing after it counts
