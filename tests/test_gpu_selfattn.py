@@ -145,6 +145,32 @@ def test_scale_at_the_maximum_and_below(dgq, oracle):
     assert float(out.abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("d", [8, 24, 40, 64, 72, 80, 160])
+def test_scale_of_zero_or_less_among_others(dgq, d):
+    """A prompt whose scale is zero or negative has a product of exact zeros, its own values however large, and the
+    prompt beside it the product, the codes and the maximum that it has with no such neighbour.  Stacked and separate
+    parts of V^T, whole and half steps, the wide kernel."""
+    import torch
+    c = di.selfattn_case(70 + d, 3, 70, 2, d)
+    c["V"][0, 5] = 3.4e38                                  # a bf16 piece of it is infinite
+    q, k, v = _dev(c["Q"]), _dev(c["K"]), _dev(c["V"])
+
+    def call(scales):
+        s_out = torch.zeros(3, device="cuda")
+        codes = torch.zeros((3, 2, 70, 70), dtype=torch.uint8, device="cuda")
+        out = dgq.dgq_selfattn_logq(q, k, v, 8, torch.tensor(scales, device="cuda"), scale_out=s_out, codes_dump=codes)
+        bare = dgq.dgq_selfattn_logq(q, k, v, 8, torch.tensor(scales, device="cuda"))
+        torch.cuda.synchronize()
+        assert torch.equal(out[1:], bare[1:])              # (the first may hold infinities and what comes of them)
+        return out, s_out, codes
+
+    out, s_out, codes = call([0.0, 0.5, -1.0])
+    alone, s_alone, codes_alone = call([1.0, 0.5, 0.25])
+    assert int(torch.count_nonzero(out[0])) == 0 and int(torch.count_nonzero(out[2])) == 0
+    assert int(torch.count_nonzero(out[1])) > 0
+    assert torch.equal(out[1], alone[1]) and torch.equal(codes[1], codes_alone[1]) and torch.equal(s_out, s_alone)
+
+
 def test_on_quantized_values(dgq, oracle):
     """A^ V^: the value tensor through dgq_quantize_value first (Section 3.3)."""
     import torch
