@@ -705,8 +705,10 @@ struct SCfg {
     static constexpr int STAGES = 3 + LEAD;
     // direct-to-LDS loads per wave and tile (8 waves): sweep A copies the K part, sweep B all
     static constexpr int LA = K_CHUNKS / 8, LB = (TILE_CHUNKS + 7) / 8;
-    // wavefronts per SIMD the registers are budgeted for: the query pieces and the output
-    // blocks of a wide head take most of the file
+    // wavefronts per SIMD that the registers must leave room for: one workgroup is two, and the query pieces and
+    // output blocks of a wide head take most of the file.  Up to 64 dims two workgroups, four wavefronts per SIMD,
+    // are to share a CU, so no kernel without the code dump (which is not timed) may take more than 128 registers:
+    // 40 and 48 dims take 125, 56 and 64 take 127, which a test of the compiled kernels holds them to.
     static constexpr int OCC = KS <= 4 ? 2 : 1;
 };
 constexpr int kSWaves = 8;  // wavefronts per workgroup: 256 queries share every tile

@@ -2,7 +2,9 @@
 
 The ring's stages are written by copies that the wait counts of LDS reads do not see: a wave may pass the barrier in
 front of such a copy only with all its reads back, by a wait that stands with the barrier and not by the chance that
-something in front of it needed the data."""
+something in front of it needed the data.
+
+And up to 64 dims two workgroups of eight wavefronts are to share a CU, for which nothing in the source asks."""
 import glob
 import os
 import re
@@ -56,3 +58,16 @@ def test_barriers_wait_for_the_lds_reads(code_object):
                 i -= 1
                 assert not code[i].startswith(("ds_", "global_")), (name, code[i])
             assert "lgkmcnt(0)" in code[i - 1], (name, code[i - 1])
+
+
+def test_registers_leave_room_for_two_workgroups(code_object):
+    """512 registers to a SIMD, four wavefronts: at most 128 each, and nothing spilled."""
+    notes = subprocess.check_output([LLVM + "llvm-readelf", "--notes", code_object], text=True)
+    counts = {}
+    for kernel in notes.split("- .agpr_count:")[1:]:
+        name = re.search(r"\.name:\s+(\S*)", kernel)[1]
+        width = re.search(r"k_selfattnINS0_4SCfgILi(\d+)ELb[01]EEELb0", name)
+        assert "k_selfattnI" not in name or re.search(r"\.private_segment_fixed_size:\s+0\b", kernel), name
+        if width and int(width[1]) <= 4:
+            counts[name] = int(re.search(r"\.vgpr_count:\s+(\d+)", kernel)[1]) + int(kernel.split()[0])
+    assert len(counts) == 8 and max(counts.values()) <= 128, counts
