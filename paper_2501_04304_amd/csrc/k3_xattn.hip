@@ -654,8 +654,10 @@ bool mfma_shape(int32_t d, int32_t nk) {
 // LDS will hold:
 //   [Kh | Kl]  32 keys x PITCH   fp16 hi / lo of K log2(e) / sqrt(d) (64, 128 or 192 dims,
 //                                zero-padded)
-//   [Vh | Vl]  DV dims x 64 B    bf16 hi / lo of s_b V^T, the 32 key slots of a tile in the
-//                                order the accumulator registers of S^T hold them
+//   [Vh | Vl]  64-byte rows      bf16 hi / lo of s_b V^T, the 32 key slots of a tile in the
+//                                order the accumulator registers of S^T hold them: VDIMS rows
+//                                of the high part (whole blocks of 32, or, stacked, the head's
+//                                dims), as many of the low part, zeros up to 32 NV rows
 // with the 16-byte slots of every row XOR-permuted by row bits, so that the 16-byte fragment
 // reads of 32 consecutive rows spread over all banks.  The second kernel gives each of its
 // eight wavefronts 32 queries (their fp16 pieces stay in registers) and sweeps the key tiles
@@ -667,20 +669,29 @@ bool mfma_shape(int32_t d, int32_t nk) {
 // 24 KB of cache traffic per wavefront and tile pair and the texture path, not the matrix
 // cores, set the pace: 5.8 ms on 16 x 10 x 4096 x 64.)
 //
-// What bounds it: the matrix cores, and the clock they leave (1.4 - 1.7 GHz).  So padding is kept out of the
+// What bounds it: matrix and vector work, and how far the one runs beside the other.  Of the clocks of
+// 16 x 4096 x 10 x 64 the matrix cores are busy 78 % and the vector pipes 47 % (four wavefronts per SIMD, 1.3 - 1.5
+// GHz), of those of 2 x 4096 x 8 x 40 46 % and 40 %, almost one after the other: that launch is one workgroup per CU,
+// two wavefronts per SIMD, which a barrier per tile keeps in phase (2.0 GHz).  So padding is kept out of the
 // products.  A head of an odd number of eights of dims (8, 24, 40, 56, 72) has half a 16-dim step left: its
 // three products are two, [Kh Kh] [Qh Ql]^T and [Kl 0] [Qh 0]^T, the lane halves reading the same eight dims
 // of K.  And where the high and the low part of V^T, stacked, fill fewer 32-row blocks than each by itself,
 // they are stacked (row t high, row d + t low, summed at the end; d % 8 = 0 puts the two into the same lane).
 // 40 dims: 8 + 8 + 6 instructions per 32 x 32 tile where 9 + 9 + 8 were.
-// And the products of tile kt + 1 are issued among the exponentials or codes of tile kt, from which they are
-// independent: at 2 x 8 x 4096 x 40 the launch is one workgroup per CU, two wavefronts per SIMD, which a
-// barrier per tile keeps in phase, so that nobody else's vector work would fill the matrix instructions' time.
-// Measured, the call before and now, us: 2 x 8 x 4096 x 40 211 -> 189; in another run (B x N x H x d)
-// 8 x 1024 x 10 x 40 99.9 -> 88.4, 2 x 2000 x 8 x 24 83.6 -> 70.6, 2 x 2100 x 8 x 48 105 -> 94,
-// 2 x 1024 x 8 x 80 77.7 -> 71.5, 16 x 4096 x 10 x 64 2310 -> 2234.  The codes have the same bits as without
-// the packing.  Kept relative to the first tile's maximum as the products' start value, the row sum saved a
-// subtraction per logit and the maxima (183 us), but moved one code in 10^6 across its rounding boundary.
+// And the products of tile kt + 1 stand in the step of tile kt's exponentials or codes, from which they are
+// independent.  How far they mix is the compiler's choice: sweep B of 64 dims alternates them, with 40 dims half of a
+// tile's codes stand before the first product; in sweep A, whose exponentials need no memory, those of every other
+// step are moved over the barrier into the next, so that (40 dims) one step holds 8 matrix and 3 vector
+// instructions and the next 8 and 127.
+// Measured in turn with the loop before, the call in us (B x N x H x d): 2 x 4096 x 8 x 40 206 -> 186,
+// 8 x 1024 x 10 x 40 93.6 -> 85.3, 2 x 1024 x 8 x 80 77.2 -> 71.4, 16 x 4096 x 10 x 64 2242 -> 2195, and, where
+// narrow heads lose a workgroup per CU to the registers, 16 x 4096 x 10 x 8 994 -> 778, x 16 1044 -> 890, x 24
+// 1331 -> 1205, x 32 1383 -> 1315.  The codes were compared at widths 8 to 160, thirteen shapes from 1 to 2048
+// tokens and both code widths, 1.5e8 to a width, and had the same bits (whether the half step's sum may round
+// differently is the matrix core's affair; what is promised is the oracle's codes 2^-13 from a boundary and
+// farther), the products the same but for 3e-7 where V^T is stacked.  Kept relative to the first tile's maximum as
+// the products' start value, the row sum saved a subtraction per logit and the maxima (183 us for 189), but moved
+// one code in 10^6 across its rounding boundary.
 template <int KS_, bool HALF_ = false>
 struct SCfg {
     static constexpr int KS = KS_;
@@ -838,7 +849,7 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     // halves take the same eight, as [Qh Ql] and [Qh 0] --------------------------------------------
     u32x4 qh[KS], ql[KS];
     {
-        const float *p = q + ((int64_t)b * N * H + head) * d + (int64_t)(valid ? qi : N - 1) * hs ;
+        const float *p = q + ((int64_t)b * N * H + head) * d + (int64_t)(valid ? qi : N - 1) * hs;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const bool half = CF::HALF && s == KS - 1;
@@ -898,8 +909,9 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     // S^T of tile kt for the wave's 32 queries, in log2 units
     auto s_tile = [&](int32_t kt, v16f &sm) __attribute__((always_inline)) {
         const uint8_t *st = ring + (kt % STAGES) * CF::TILE_BYTES;
-        // all fragments of a narrow head are read up front; a wide head (whose query pieces
-        // and output blocks fill the register file) reads them one step ahead of their MFMAs
+        // the fragments of a narrow head have registers of their own, so that the compiler may read them as early
+        // as it likes (it reads them in pairs, a step or two ahead of their MFMAs); a wide head, whose query
+        // pieces and output blocks fill the register file, reads them one step ahead
         constexpr int NF = KS <= 4 ? KS : 2;
         u32x4 fh[NF], fl[NF];
         auto frag = [&](int s) __attribute__((always_inline)) {
@@ -1023,8 +1035,8 @@ __global__ __launch_bounds__(64 * kSWaves, CF::OCC) void k_selfattn(
     // codes of tile kt from its logits, and its share of the product
     auto code_tile = [&](int32_t kt, const v16f &sm) __attribute__((always_inline)) {
         const uint8_t *st = ring + (kt % STAGES) * CF::TILE_BYTES + CF::K_BYTES;
-        // V^T fragments of this tile.  Narrow heads: all read before the code arithmetic that
-        // hides them; wide heads: each right before its MFMAs (registers)
+        // V^T fragments of this tile.  Narrow heads: with registers of their own, read where the compiler finds
+        // room among the codes; wide heads: each right before its MFMAs (registers)
         constexpr bool V_AHEAD = KS <= 4;
         auto v_frag = [&](int vb, int u) __attribute__((always_inline)) {
             return *reinterpret_cast<const u32x4 *>(st + vb * 32 * 64 + (v_off ^ (u << 5)));
